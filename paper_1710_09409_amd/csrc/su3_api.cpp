@@ -657,7 +657,23 @@ static std::mutex g_tune_mu;
 static std::map<Key, su3_launch> g_tuned;
 static bool g_cache_loaded = false;
 
-static su3_launch default_launch(int expr, int prec, int layout)
+// Bytes a site-local call of V sites reads and writes.
+static int64_t site_call_bytes(int expr, int prec, int64_t V)
+{
+    return V * entries_of(prec) * 2 * real_bytes(prec) * (operands_of(expr) + 1);
+}
+
+// Calls of up to this many bytes leave their operands in the 256 MiB
+// Infinity Cache, where a program that comes back to its fields finds them.
+// Measured with three sets of fields in turn: cached loads win below (FP32
+// MUL 24^3 x 48, 143 MB: 23.6 us against 25.7 with nontemporal loads), lose
+// above (FP32 MUL3 24^3 x 48, 191 MB: 35.3 against 33.6).  On fields that
+// are in no cache cached loads cost up to 5 % (FP32 24^4: 14.3 against 13.6).
+static const int64_t kCachedBytes = (int64_t)160 * 1000 * 1000;
+
+// The launch of a call that nothing tuned or set: V sites of the key's
+// expression, precision and layout.
+static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
 {
     su3_launch c;
     c.block = 64;
@@ -669,6 +685,29 @@ static su3_launch default_launch(int expr, int prec, int layout)
     c.occupancy = layout == SU3_LAYOUT_AOS ? 0 : 5;
     c.schedule = layout == SU3_LAYOUT_AOS ? 0 : 1;
     c.sites_per_lane = 0;
+    const bool site = expr >= SU3_EXPR_MUL && expr <= SU3_EXPR_APB_AB;
+    if (site && layout == SU3_LAYOUT_AOS) {
+        // Whole tiles through LDS: FP64 32^4 70 us, against 679 us read
+        // directly, site by site.  Calls of up to kCachedBytes keep their
+        // loads cached and take every wave that fits (FP32 24^4: 11.4 us
+        // against 12.9 with nontemporal loads).  Beyond, double streams best
+        // with 6 waves per CU and write-through stores (FP64 40^4: 170 us;
+        // 5 waves 173, 8 waves 178; FP64 48^4 358 and 371), the others with
+        // 8 (FP32 40^4 85.7 us, uncapped 86.6), four single or double
+        // operands with 5 (FP32 MULADD 40^4: 140.9 us, uncapped 152).
+        const bool dbl = prec == SU3_F64, four = expr == SU3_EXPR_MULADD;
+        c.lds_stage = 1;
+        if (site_call_bytes(expr, prec, V) <= kCachedBytes) {
+            c.occupancy = 0;
+            c.nontemporal = 2;
+        } else if (dbl && !four) {
+            c.block = 128;
+            c.occupancy = 3;
+            c.nontemporal = 7;
+        } else {
+            c.occupancy = four && prec != SU3_F16_F32ACC ? 5 : 8;
+        }
+    }
     if (expr == SU3_EXPR_PROGRAM || expr == SU3_EXPR_PROGRAM_SCALAR) {
         c.block = 128;
         c.occupancy = 0;
@@ -778,7 +817,7 @@ static su3_launch lookup_launch(int expr, int prec, int layout, int lanes,
     auto it = g_tuned.find(Key(expr, prec, layout, lanes, vbucket(V)));
     if (it != g_tuned.end())
         return it->second;
-    return default_launch(expr, prec, layout);
+    return default_launch(expr, prec, layout, V);
 }
 
 // JSON cache: one object per line with integer fields.
@@ -955,7 +994,7 @@ static su3_status launch_item(su3_field *z, int expr,
                                                device_cus(z->device));
         a.ngroups = (int32_t)z->V;
         e = launch_site_lds(z->prec, expr, c.nontemporal, c.block, (int)grid,
-                            a, st);
+                            occupancy_reserve(z->device, c.occupancy), a, st);
     } else {
         // S sites per lane must sit in one lane-block: the natural count
         // (or 1 where the blocks are shorter), or the launch's own count
@@ -1648,7 +1687,7 @@ static std::vector<su3_launch> candidates(int layout, int expr, int prec)
 static std::vector<su3_launch> dslash_candidates(int cbytes, int lx, int nsub)
 {
     std::vector<su3_launch> out;
-    su3_launch c = default_launch(SU3_EXPR_DSLASH, SU3_F64, SU3_LAYOUT_SOA);
+    su3_launch c = default_launch(SU3_EXPR_DSLASH, SU3_F64, SU3_LAYOUT_SOA, 0);
     c.nontemporal = 2;
     // virtual nodes: one site per lane in index order, or row tiles
     for (int walk : {1, 4, 8})
@@ -1702,7 +1741,7 @@ static std::vector<su3_launch> dslash_candidates(int cbytes, int lx, int nsub)
 static std::vector<su3_launch> program_candidates()
 {
     std::vector<su3_launch> out;
-    su3_launch c = default_launch(SU3_EXPR_PROGRAM, SU3_F64, SU3_LAYOUT_SOA);
+    su3_launch c = default_launch(SU3_EXPR_PROGRAM, SU3_F64, SU3_LAYOUT_SOA, 0);
     for (int b : {64, 128, 256})
         for (int occ : {0, 2, 3, 4, 6, 8})
             for (int nt : {0, 2, 3}) {
@@ -1816,7 +1855,7 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
         }
     }
     size_t turn = 0;
-    su3_launch win = default_launch(expr, prec, layout);
+    su3_launch win = default_launch(expr, prec, layout, s.V);
     double win_us = 1e300;
     // expression programs are timed on the streaming product a*b, those
     // with a scalar result on the trace of a product
@@ -2246,7 +2285,7 @@ extern "C" su3_status su3_batch_autotune(const su3_expr *exprs,
     for (int i = 0; i < n; ++i)
         if (z[i])
             total += z[i]->V;
-    su3_launch win = default_launch(exprs[0], z[0]->prec, z[0]->layout);
+    su3_launch win = default_launch(exprs[0], z[0]->prec, z[0]->layout, total);
     double win_us = 1e300;
     for (const su3_launch &c : batch_candidates()) {
         su3_batch *b = nullptr;

@@ -107,9 +107,10 @@ inline bool sites_compiled(int prec, int expr, int S)
 hipError_t launch_site(int prec, int expr, int sites_per_lane, int nt,
                        int sched, int block, int grid, size_t shm,
                        const SiteArgs &a, hipStream_t stream);
-// AoS with LDS staging: one lane per site, `block` sites per workgroup.
+// AoS with LDS staging: one lane per site, `block` sites per workgroup;
+// `reserve` caps the workgroups per CU as `shm` of launch_site.
 hipError_t launch_site_lds(int prec, int expr, int nt, int block, int grid,
-                           const SiteArgs &a, hipStream_t stream);
+                           size_t reserve, const SiteArgs &a, hipStream_t stream);
 // Batched launch over `ntiles` tiles of `tile_sites` sites.  queue ==
 // nullptr: `grid` workgroups each taking tiles blockIdx.x, blockIdx.x +
 // grid, ... (one per tile when grid == ntiles); else a persistent grid

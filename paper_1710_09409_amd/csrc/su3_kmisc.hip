@@ -12,10 +12,10 @@ hipError_t launch_shift_p0(int, int, int, int, int, size_t, const ShiftArgs &, h
 hipError_t launch_shift_p1(int, int, int, int, int, size_t, const ShiftArgs &, hipStream_t);
 hipError_t launch_shift_p2(int, int, int, int, int, size_t, const ShiftArgs &, hipStream_t);
 hipError_t launch_shift_p3(int, int, int, int, int, size_t, const ShiftArgs &, hipStream_t);
-hipError_t launch_site_lds_p0(int, int, int, int, const SiteArgs &, hipStream_t);
-hipError_t launch_site_lds_p1(int, int, int, int, const SiteArgs &, hipStream_t);
-hipError_t launch_site_lds_p2(int, int, int, int, const SiteArgs &, hipStream_t);
-hipError_t launch_site_lds_p3(int, int, int, int, const SiteArgs &, hipStream_t);
+hipError_t launch_site_lds_p0(int, int, int, int, size_t, const SiteArgs &, hipStream_t);
+hipError_t launch_site_lds_p1(int, int, int, int, size_t, const SiteArgs &, hipStream_t);
+hipError_t launch_site_lds_p2(int, int, int, int, size_t, const SiteArgs &, hipStream_t);
+hipError_t launch_site_lds_p3(int, int, int, int, size_t, const SiteArgs &, hipStream_t);
 }  // namespace su3i
 
 namespace su3k {
@@ -233,13 +233,13 @@ hipError_t launch_shift(int prec, int mode, int nt, int sched, int block,
 }
 
 hipError_t launch_site_lds(int prec, int expr, int nt, int block, int grid,
-                           const SiteArgs &a, hipStream_t st)
+                           size_t reserve, const SiteArgs &a, hipStream_t st)
 {
     switch (prec) {
-    case F64: return launch_site_lds_p0(expr, nt, block, grid, a, st);
-    case F32: return launch_site_lds_p1(expr, nt, block, grid, a, st);
-    case F16: return launch_site_lds_p2(expr, nt, block, grid, a, st);
-    case C12: return launch_site_lds_p3(expr, nt, block, grid, a, st);
+    case F64: return launch_site_lds_p0(expr, nt, block, grid, reserve, a, st);
+    case F32: return launch_site_lds_p1(expr, nt, block, grid, reserve, a, st);
+    case F16: return launch_site_lds_p2(expr, nt, block, grid, reserve, a, st);
+    case C12: return launch_site_lds_p3(expr, nt, block, grid, reserve, a, st);
     }
     return hipErrorInvalidValue;
 }
