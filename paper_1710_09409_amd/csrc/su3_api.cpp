@@ -708,6 +708,70 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
             c.occupancy = four && prec != SU3_F16_F32ACC ? 5 : 8;
         }
     }
+    if (site && layout != SU3_LAYOUT_AOS) {
+        // Up to kCachedBytes: cached loads, every wave that fits (half MUL3
+        // 24^4, 48 MB: 8.8 us against 13.6 with nontemporal loads and 5
+        // waves per CU).  Beyond, fewer waves and streaming stores: double
+        // 5 waves (48^4 MUL 352 us; 8 waves 382, uncapped 415), single and
+        // two-row 8 up to half a GB (FP32 32^4 41.5 us, 5 waves 46.6) and 5
+        // from there (FP32 48^4 180 us, 8 waves 188), half 8 (MUL3 48^4
+        // 124 us, 5 waves 165).  Write-through stores gain 1-2 % where the
+        // call exceeds the cache several times, and lose below.
+        const int64_t bytes = site_call_bytes(expr, prec, V);
+        const bool dbl = prec == SU3_F64, half = prec == SU3_F16_F32ACC;
+        const bool large = bytes > (int64_t)512 * 1000 * 1000;
+        if (bytes <= kCachedBytes) {
+            c.occupancy = 0;
+            c.nontemporal = 2;
+            // (half MUL3 7.2 us against 8.3 row by row at 229425 sites;
+            // MULADD, with four operands of two sites, the other way round)
+            c.schedule = !half || expr == SU3_EXPR_MULADD;
+        } else {
+            c.occupancy = dbl || (large && !half) ? 5 : 8;
+            c.nontemporal = dbl || large ? 7 : 3;
+        }
+        // Entry planes a multiple of 2 MiB apart (2 to 16 MiB: power-of-two
+        // lattices) meet in the same memory channels: there each XCD takes a
+        // range of its own (FP64 32^4 73 us against 81, 16^3 x 32 9.0 against
+        // 10.8).  Planes of 32 MiB lose by it (FP64 32^3 x 64: 155 against
+        // 141), and so does half with 3-4 operands, whose lanes take 8 bytes.
+        if (layout == SU3_LAYOUT_SOA) {
+            const int64_t plane = (V + 63) / 64 * 64 * 2 * real_bytes(prec);
+            c.xcd_remap = plane % (2 << 20) == 0 && plane <= (16 << 20) &&
+                          !(half && operands_of(expr) > 2);
+        }
+    }
+    if (expr == SU3_EXPR_CSHIFT || expr == SU3_EXPR_MUL_SHIFTED) {
+        // One site per lane: 8 (single) or 4 bytes (half) per access instead
+        // of 16, so it takes 16 waves per CU to keep as many bytes in flight
+        // (FP32 24^3 x 48: 24.7 us against 35.1 with 5; half 48^4 98.6
+        // against 220).  Double needs fewer the larger the call (product
+        // 48^4: 5 waves 377 us, 10 waves 391; 24^3 x 48: 10 waves 49.8 us, 5
+        // waves 52.7; copy 48^4 6 waves 254, 5 waves 262).  Stores and loads
+        // are cached below 64 to 100 MB (half copy 32^4: 12 us against 19).
+        // AoS reads every line once per entry, so its loads always stay
+        // cached (FP64 32^4: 103 us against 452).
+        const bool product = expr == SU3_EXPR_MUL_SHIFTED, dbl = prec == SU3_F64;
+        const int64_t bytes = V * entries_of(prec) * 2 * real_bytes(prec) * (product ? 3 : 2);
+        const int64_t MB = 1000 * 1000;
+        c.schedule = dbl || prec == SU3_C12_F32;
+        c.block = 256;
+        c.occupancy = 4;
+        c.nontemporal = bytes <= 100 * MB ? 0 : prec == SU3_F32 ? 7 : 3;
+        if (layout == SU3_LAYOUT_AOS) {
+            c.block = dbl || prec == SU3_F32 ? 128 : 256;
+            c.occupancy = dbl || prec == SU3_F32 ? 3 : prec == SU3_F16_F32ACC ? 0 : 4;
+            c.nontemporal = 0;
+        } else if (dbl && product && bytes > 100 * MB) {
+            c.block = bytes > 200 * MB && bytes <= 512 * MB ? 128 : 64;
+            c.occupancy = bytes > 200 * MB ? 5 : 0;
+            c.nontemporal = bytes > 200 * MB ? 7 : 3;
+        } else if (dbl && !product) {
+            c.block = 128;
+            c.occupancy = bytes <= 64 * MB ? 5 : 3;
+            c.nontemporal = bytes <= 64 * MB ? 0 : bytes <= 200 * MB ? 3 : 7;
+        }
+    }
     if (expr == SU3_EXPR_PROGRAM || expr == SU3_EXPR_PROGRAM_SCALAR) {
         c.block = 128;
         c.occupancy = 0;
