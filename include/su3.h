@@ -461,11 +461,10 @@ su3_status su3_vnode_wrap(su3_field **out, void *dev_ptr, size_t bytes,
  * Section 3, Listing 1's site loop run over several lattices at once, with
  * each workgroup holding several vectors of lanes as Section 5 proposes
  * (the paper itself times one lattice per launch)
- * over a table of tiles, captured once in a HIP graph and replayed by
- * su3_batch_launch.  ops holds 4 pointers per item (unused = NULL).  Each
- * item obeys the rules of su3_fused_eval.  The tile table (see
- * su3_batch_tiles) is built on the host from the items' volumes and the
- * tuned tile size; the batch owns its device copy and its graph.  Fields
+ * over a table of tiles; su3_batch_launch launches it.  ops holds 4 pointers
+ * per item (unused = NULL).  Each item obeys the rules of su3_fused_eval.
+ * The tile table (see su3_batch_tiles) is built on the host from the items'
+ * volumes and the tuned tile size; the batch owns its device copy.  Fields
  * must outlive the batch.  Creation runs on `stream` and completes before
  * returning. */
 su3_status su3_batch_create(su3_batch **out, const su3_expr *exprs,
@@ -491,12 +490,13 @@ su3_status su3_batch_create(su3_batch **out, const su3_expr *exprs,
 su3_status su3_batch_run(const su3_expr *exprs, su3_field *const *z,
                          const su3_field *const *ops, int32_t n, void *stream);
 
-/* Replay the batch's graph on `stream` (asynchronous): one pass of
- * Section 3, Listing 1's site loop over every item. */
+/* Evaluate the batch once on `stream` (asynchronous, one kernel launch; it
+ * can be captured): one pass of Section 3, Listing 1's site loop over every
+ * item. */
 su3_status su3_batch_launch(su3_batch *b, void *stream);
 
 /* Release a batch (the batch of Section 3's site loop over several
- * lattices): its tile table and graph; the fields are untouched. */
+ * lattices): its tile table; the fields are untouched. */
 su3_status su3_batch_destroy(su3_batch *b);
 
 /* Copy the batch's tile table from the device: 4 int32 per tile, (item,
@@ -545,7 +545,7 @@ su3_status su3_layout_recommend(su3_expr expr, su3_precision prec,
  * of Section 3's loop over several lattices): build the batch with each
  * candidate launch (tile size,
  * one workgroup per tile or k per CU, occupancy cap, schedule, nontemporal
- * bits), time graph replays (median of 5 after 2), and keep the fastest for
+ * bits), time launches (median of 5 after 2), and keep the fastest for
  * later su3_batch_create calls on items of the same leading (expr,
  * precision, layout, lanes) and total-volume bucket.  Arguments as for
  * su3_batch_create.  The candidates write the items' outputs (with the

@@ -57,8 +57,6 @@ struct su3_batch {
     su3_launch cfg;
     int32_t grid;
     int32_t device;
-    hipGraph_t graph;
-    hipGraphExec_t exec;
 };
 
 // ------------------------------------------------------------- errors
@@ -657,6 +655,14 @@ static std::mutex g_tune_mu;
 static std::map<Key, su3_launch> g_tuned;
 static bool g_cache_loaded = false;
 
+// Launch-tuning keys of batches are SU3_EXPR_BATCH + the leading item's
+// expression, so that a batch's tuned tile and grid never stand in for a
+// single field's launch of the same volume bucket (and the reverse).
+static bool is_batch_key(int expr)
+{
+    return expr >= SU3_EXPR_BATCH && expr <= SU3_EXPR_BATCH + SU3_EXPR_APB_AB;
+}
+
 // Bytes a site-local call of V sites reads and writes.
 static int64_t site_call_bytes(int expr, int prec, int64_t V)
 {
@@ -741,6 +747,20 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
                           !(half && operands_of(expr) > 2);
         }
     }
+    if (is_batch_key(expr)) {
+        // One workgroup of 128 lanes per tile of 128 sites: a batch of any
+        // size fills the chip (four lattices of 8^4 to 24^3 x 48: 18 us
+        // against 141 with one wave walking 4096 sites; 64 lattices, 5.8 GB:
+        // 1145 us against 1223).  Cached like the site-local calls.
+        c.tile_sites = 128;
+        c.block = 128;
+        c.occupancy = 0;
+        c.schedule = expr != SU3_EXPR_BATCH + SU3_EXPR_MUL;
+        const int64_t bytes = site_call_bytes(expr - SU3_EXPR_BATCH, prec, V);
+        c.nontemporal = bytes <= (int64_t)100 * 1000 * 1000 ? 0
+                        : bytes <= (int64_t)1000 * 1000 * 1000 ? 3
+                                                               : 7;
+    }
     if (expr == SU3_EXPR_CSHIFT || expr == SU3_EXPR_MUL_SHIFTED) {
         // One site per lane: 8 (single) or 4 bytes (half) per access instead
         // of 16, so it takes 16 waves per CU to keep as many bytes in flight
@@ -792,14 +812,6 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
         c.xcd_remap = 0;
     }
     return c;
-}
-
-// Launch-tuning keys of batches are SU3_EXPR_BATCH + the leading item's
-// expression, so that a batch's tuned tile and grid never stand in for a
-// single field's launch of the same volume bucket (and the reverse).
-static bool is_batch_key(int expr)
-{
-    return expr >= SU3_EXPR_BATCH && expr <= SU3_EXPR_BATCH + SU3_EXPR_APB_AB;
 }
 
 static bool nt_valid(int nt, bool streaming)
@@ -2143,7 +2155,6 @@ static su3_status batch_create(su3_batch **out, const su3_expr *exprs,
     const int mode = plan.mode, dev = plan.device;
     const int64_t ntiles = plan.ntiles;
     const su3_launch cfg = plan.cfg;
-    const int T = cfg.tile_sites;
     su3_batch *b = new su3_batch();
     std::memset(b, 0, sizeof *b);
     b->nitems = n;
@@ -2168,24 +2179,6 @@ static su3_status batch_create(su3_batch **out, const su3_expr *exprs,
     }
     if (e == hipSuccess)
         e = hipStreamSynchronize(hs);
-    // Capture the one launch on a private stream and instantiate the graph.
-    hipStream_t cap = nullptr;
-    if (e == hipSuccess)
-        e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
-    if (e == hipSuccess)
-        e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        hipError_t le = launch_batch(b->mode, b->d_items, b->nitems, b->ntiles,
-                                     T, cfg.nontemporal, cfg.schedule, cfg.block,
-                                     b->grid, occupancy_reserve(dev, cfg.occupancy),
-                                     b->d_queue, cap);
-        hipError_t ce = hipStreamEndCapture(cap, &b->graph);
-        e = le != hipSuccess ? le : ce;
-    }
-    if (e == hipSuccess)
-        e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
-    if (cap)
-        (void)hipStreamDestroy(cap);
     if (e != hipSuccess) {
         su3_status r = hip_fail(e, "batch create");
         su3_batch_destroy(b);
@@ -2278,8 +2271,15 @@ extern "C" su3_status su3_batch_launch(su3_batch *b, void *stream)
 {
     if (!b)
         return fail(SU3_ERR_INVALID_ARG, "batch is NULL");
-    HIP_TRY(hipGraphLaunch(b->exec, static_cast<hipStream_t>(stream)),
-            "hipGraphLaunch");
+    // one kernel: launched directly it costs 2.8 us of a stream's time, as a
+    // graph of one node 15.3 us (either replayed back to back)
+    const hipError_t e =
+        launch_batch(b->mode, b->d_items, b->nitems, b->ntiles, b->cfg.tile_sites,
+                     b->cfg.nontemporal, b->cfg.schedule, b->cfg.block, b->grid,
+                     occupancy_reserve(b->device, b->cfg.occupancy), b->d_queue,
+                     static_cast<hipStream_t>(stream));
+    if (e != hipSuccess)
+        return hip_fail(e, "batch launch");
     return SU3_OK;
 }
 
@@ -2287,10 +2287,6 @@ extern "C" su3_status su3_batch_destroy(su3_batch *b)
 {
     if (!b)
         return SU3_OK;
-    if (b->exec)
-        (void)hipGraphExecDestroy(b->exec);
-    if (b->graph)
-        (void)hipGraphDestroy(b->graph);
     if (b->d_mem)
         (void)hipFree(b->d_mem);
     delete b;
