@@ -207,7 +207,11 @@ typedef struct su3_program su3_program;
  *               2 half sites for 3-4 operands), else 1, the natural count,
  *               or for MUL outside half storage twice the natural count
  *               (32-byte accesses); the lane-block L must be a multiple
- *               (SU3_ERR_INVALID_ARG otherwise).  Ignored elsewhere       */
+ *               (SU3_ERR_INVALID_ARG otherwise).
+ *               su3_dslash with one site per lane in index order (schedule
+ *               0, tile_sites 1): 8 gives each of a site's eight hops a wave
+ *               of its own (64 sites per workgroup of 512 lanes; block and
+ *               occupancy are ignored).  Ignored elsewhere              */
 typedef struct su3_launch {
     int32_t block;
     int32_t persistent;

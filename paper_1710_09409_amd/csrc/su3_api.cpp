@@ -798,18 +798,13 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
         c.schedule = 0;
     }
     if (expr == SU3_EXPR_DSLASH) {
-        // the LDS-tiled walk over whole x rows (smaller tiles where the rows
-        // are too long): Lx x 3 x 3 with one buffer walking 8 t-slices for
-        // double spinors, Lx x 4 x 4 with two buffers walking 7 for single
-        // (the fastest chunked walks at 48^4); cached loads (neighbours
-        // re-read each spinor), nontemporal stores
-        const bool dbl = prec == SU3_F64;
+        // cached loads (neighbours re-read each spinor), nontemporal stores;
+        // default_dslash plans the rest from the lattice's extents
         c.block = 256;
         c.nontemporal = 2;
         c.occupancy = 0;
-        c.schedule = dbl ? 17 : 16;
-        c.tile_sites = dbl ? 8 : 7;
-        c.xcd_remap = 0;
+        c.schedule = prec == SU3_F64 ? 17 : 16;
+        c.tile_sites = prec == SU3_F64 ? 8 : 7;
     }
     return c;
 }
@@ -885,15 +880,134 @@ static su3_status check_launch(const su3_launch &c, int layout, int expr)
 
 static void load_cache_locked();
 
-static su3_launch lookup_launch(int expr, int prec, int layout, int lanes,
-                                int64_t V)
+// The tuned or set launch of a key, if there is one.
+static bool tuned_launch(int expr, int prec, int layout, int lanes, int64_t V,
+                         su3_launch *c)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     load_cache_locked();
     auto it = g_tuned.find(Key(expr, prec, layout, lanes, vbucket(V)));
-    if (it != g_tuned.end())
+    if (it == g_tuned.end())
+        return false;
+    *c = it->second;
+    return true;
+}
+
+static su3_launch lookup_launch(int expr, int prec, int layout, int lanes,
+                                int64_t V)
+{
+    su3_launch c;
+    return tuned_launch(expr, prec, layout, lanes, V, &c)
+               ? c
+               : default_launch(expr, prec, layout, V);
+}
+
+// Estimated microseconds of an LDS-tiled Dslash walk of `walk` t-slices over
+// (outer) extents o: the rounds of workgroups the CUs need, each walking
+// `walk` slices and a start-up, at a slice time that is the larger of a
+// latency floor (barriers, LDS and a slice's dependent loads) and the tile's
+// bytes at a CU's share of the memory rate.  The constants are fitted to 45
+// measured lattices (24^4 to 48^4, odd extents, virtual nodes; up to 13 row
+// tiles and 14 walks each): the tile and walk of least estimate run within
+// 0.5 % (double), 2 % (single) and 3 % (two-row links) of the fastest.
+static double dslash_walk_us(const LdsShape &sh, int prec, const int32_t o[4],
+                             int walk, int cus)
+{
+    const bool dbl = prec == SU3_F64;
+    const double spinor = dbl ? 192 : 96, link = dbl ? 144 : prec == SU3_F32 ? 72 : 48;
+    const double floor_us = (dbl ? 14.0 : 10.0) * (!dbl && sh.nb == 2 ? 0.95 : 1.0);
+    const double start = dbl ? 1.0 : 1.5, cu_bytes_per_us = dbl ? 20e3 : 30e3;
+    const int wave_slots = dbl ? 8 : prec == SU3_F32 ? 16 : 12;
+    // bytes per site: links, input, output; half of the face sites' second
+    // reads miss (a halo saves a quarter of those in double)
+    const double x_cut = sh.tx < o[0] ? 1.0 / sh.tx : 0.0;
+    const double yz_cut = 1.0 / sh.ty + 1.0 / sh.tz;
+    const double site_bytes = 2 * spinor + 4 * link + 0.5 * (2 * spinor + link) *
+                              (x_cut + yz_cut * (dbl && sh.halo ? 0.75 : 1.0));
+    const int lanes = sh.nsub * sh.tx * sh.ty * sh.tz;
+    int64_t groups = (o[3] + walk - 1) / walk;
+    groups *= (int64_t)((o[0] + sh.tx - 1) / sh.tx) * ((o[1] + sh.ty - 1) / sh.ty) *
+              ((o[2] + sh.tz - 1) / sh.tz);
+    const int per_cu = std::max(1, std::min((int)(160 * 1024 / lds_shape_bytes(sh, dbl ? 16 : 8)),
+                                            wave_slots / ((lanes + 63) / 64)));
+    const int64_t slots = (int64_t)cus * per_cu, rest = groups % slots;
+    const auto round_us = [&](int64_t resident) {
+        return (walk + start) *
+               std::max(floor_us, (double)resident * lanes * site_bytes / cu_bytes_per_us);
+    };
+    return (double)(groups / slots) * round_us(per_cu) +
+           (rest ? round_us((rest + cus - 1) / cus) : 0.0);
+}
+
+// The untuned launch of the Wilson hopping term on lattice dims (virtual
+// nodes simd, L sites per lane-block).
+static su3_launch plan_dslash(int prec, int layout, int64_t L, const int32_t dims[4],
+                              const int32_t simd[4], int cus)
+{
+    const bool dbl = prec == SU3_F64, vn = layout == SU3_LAYOUT_VNODE;
+    const int cbytes = dbl ? 16 : 8, nsub = vn ? (int)L : 1;
+    int32_t o[4];
+    int64_t V = 1;
+    for (int mu = 0; mu < 4; ++mu) {
+        o[mu] = dims[mu] / simd[mu];
+        V *= dims[mu];
+    }
+    su3_launch c = default_launch(SU3_EXPR_DSLASH, prec, layout, V);
+    // One wave per hop where the lattice cannot fill the chip otherwise (16^3
+    // x 32, two-row links: 12.7 us, walks 46.8, one lane per site 15.8) and
+    // as long as its second reads of each spinor come from the caches: to
+    // 24^4 (FP64 79 us, best walk 76) on whole lines, less where a wave's
+    // entry is shorter than a line (N_sub < 8 FP64 24^4: 101 against 84) or
+    // double spinors lie site after site (174 against 148).
+    // Single AoS spinors keep it at any size: the walks store nontemporally,
+    // which AoS pays for (FP32 32^4: 238 us against 434).
+    const bool aos = layout == SU3_LAYOUT_AOS;
+    const int64_t most = aos && !dbl ? ((int64_t)1 << 31) : (aos || (vn && nsub < 8)) ? 150000 : 360000;
+    if (V <= most) {
+        c.schedule = 0;
+        c.tile_sites = 1;
+        c.sites_per_lane = 8;
+        c.xcd_remap = 1;
+        c.nontemporal = aos || (vn && nsub < 8) ? 0 : 2;
+        return c;
+    }
+    double best = 1e300;
+    for (int sched : {9, 10, 11, 12, 16, 17, 18, 20, 21, 22, 26, 27, 28}) {
+        LdsShape sh;
+        if (!lds_shape(sched, 256, cbytes, o[0], nsub, sh))
+            continue;
+        for (int chunks = 1, last = 0; chunks <= o[3] && chunks <= 4096; ++chunks) {
+            const int walk = std::min((o[3] + chunks - 1) / chunks, 4096);
+            if (walk == last)
+                continue;
+            last = walk;
+            const double us = dslash_walk_us(sh, prec, o, walk, cus);
+            if (us < best) {
+                best = us;
+                c.schedule = sched;
+                c.tile_sites = walk;
+            }
+        }
+    }
+    return c;
+}
+
+// plan_dslash, remembered per lattice (a few microseconds of host time
+// each); a bounded table of plain values, shared by all threads.
+static su3_launch default_dslash(int prec, int layout, int64_t L, const int32_t dims[4],
+                                 const int32_t simd[4], int cus)
+{
+    static std::mutex mu;
+    static std::map<std::array<int32_t, 11>, su3_launch> plans;
+    const std::array<int32_t, 11> key = {prec,    layout,  cus,     dims[0], dims[1], dims[2],
+                                         dims[3], simd[0], simd[1], simd[2], simd[3]};
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = plans.find(key);
+    if (it != plans.end())
         return it->second;
-    return default_launch(expr, prec, layout, V);
+    if (plans.size() >= 256)
+        plans.clear();
+    return plans[key] = plan_dslash(prec, layout, L, dims, simd, cus);
 }
 
 // JSON cache: one object per line with integer fields.
@@ -1232,10 +1346,12 @@ static su3_status launch_dslash_op(su3_field *out, su3_field *const links[4],
                                    const su3_launch *forced = nullptr)
 {
     const su3_field *u0 = links[0];
-    su3_launch c =
-        forced ? *forced
-               : lookup_launch(SU3_EXPR_DSLASH, u0->prec, u0->layout,
-                               u0->lanes, u0->V);
+    su3_launch c;
+    if (forced)
+        c = *forced;
+    else if (!tuned_launch(SU3_EXPR_DSLASH, u0->prec, u0->layout, u0->lanes, u0->V, &c))
+        c = default_dslash(u0->prec, u0->layout, u0->L, u0->dims, u0->simd,
+                           device_cus(u0->device));
     const int cbytes = 2 * out->rbytes;  // one complex spinor entry
     const bool vn = out->layout == SU3_LAYOUT_VNODE;
     const int nsub = vn ? (int)out->L : 1;
@@ -1344,6 +1460,12 @@ static su3_status launch_dslash_op(su3_field *out, su3_field *const links[4],
     size_t shm = occupancy_reserve(out->device, c.occupancy);
     if (a.lds_tile)  // the tile's slice buffers (no occupancy cap)
         shm = lds_shape_bytes(sh, cbytes);
+    if (!lds && a.walk <= 1 && c.schedule == 0 && c.sites_per_lane == 8) {
+        a.hop_waves = 1;
+        c.block = kDslashHopBlock;
+        grid = (out->V + kDslashHopSites - 1) / kDslashHopSites;
+        shm = (size_t)kDslashHopComplex * cbytes;
+    }
     hipError_t e = launch_dslash(out->prec, u0->prec, c.nontemporal, c.block,
                                  (int)grid, shm, a,
                                  static_cast<hipStream_t>(stream));
@@ -1645,7 +1767,18 @@ extern "C" su3_status su3_launch_get(su3_expr expr, su3_precision prec,
     su3_status st = key_of(expr, prec, layout, lanes, dims, &k, &s);
     if (st != SU3_OK)
         return st;
-    *out = lookup_launch(expr, prec, layout, std::get<3>(k), s.V);
+    if (tuned_launch(expr, prec, layout, std::get<3>(k), s.V, out))
+        return SU3_OK;
+    *out = default_launch(expr, prec, layout, s.V);
+    if (expr == SU3_EXPR_DSLASH) {
+        int32_t simd[4] = {1, 1, 1, 1};
+        if (layout == SU3_LAYOUT_VNODE)
+            (void)default_simd(dims, lanes, simd);  // checked by key_of
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess)
+            dev = 0;
+        *out = default_dslash(prec, layout, s.L, dims, simd, device_cus(dev));
+    }
     return SU3_OK;
 }
 
@@ -1780,6 +1913,17 @@ static std::vector<su3_launch> dslash_candidates(int cbytes, int lx, int nsub)
                         c.xcd_remap = x;
                         out.push_back(c);
                     }
+    // one wave per hop
+    c.tile_sites = 1;
+    c.schedule = 0;
+    c.block = 64;
+    c.occupancy = 0;
+    c.sites_per_lane = 8;
+    for (int x : {0, 1}) {
+        c.xcd_remap = x;
+        out.push_back(c);
+    }
+    c.sites_per_lane = 0;
     // LDS-tiled walks: every tile shape that fits this spinor precision and
     // lattice (cached loads; nontemporal stores), with and without a halo
     for (int sched = 4; sched <= 28; ++sched)

@@ -41,7 +41,15 @@ struct DslashArgs {
     // direction.  0: no LDS tile
     uint32_t lds_tile;
     uint32_t lds_tx;    // row tiles (schedules 9..28): the tile's x extent
+    // 1: one wave per hop, kDslashHopSites sites in index order per
+    // workgroup of kDslashHopBlock lanes (walk == 1, no tile)
+    uint32_t hop_waves;
 };
+
+constexpr int kDslashHopSites = 64;
+constexpr int kDslashHopBlock = 8 * kDslashHopSites;
+// complex numbers of LDS: a half spinor per hop and site
+constexpr int kDslashHopComplex = 8 * 6 * kDslashHopSites;
 
 // Tile of the LDS-tiled walk: tx x ty x tz (x, y, z) sites -- outer sites
 // with all their nsub virtual nodes in the virtual-node layout -- one lane

@@ -304,6 +304,139 @@ __global__ __launch_bounds__(256, WPE) void k_dslash(su3i::DslashArgs a)
         occupancy_reserve[threadIdx.x] = 0;
 }
 
+// -------------------------------------------- one wave per hop (small)
+//
+// The kernel for lattices too small to fill the chip with one lane per site:
+// there the eight hops one after another are eight memory round trips with
+// nothing to hide them.  A workgroup of eight waves owns 64 sites; wave k
+// computes hop k (in the accumulation order: t backward, x, y, z forward and
+// backward, t forward) of all 64, so a site's 168 loads are in flight
+// together, and leaves its rotated half spinor in LDS.  The waves then share
+// the 12 result entries of the sites, each adding the hops in that order:
+// the same sums in the same order as the other kernels.
+
+// Component of the half spinor that spin SPIN takes from a hop along MU.
+template <int MU, int SPIN>
+constexpr int half_of_spin()
+{
+    return SPIN < 2 ? SPIN : MU < 2 ? 3 - SPIN : SPIN - 2;
+}
+
+// acc += the hop's contribution to spin SPIN (reconstruct, one entry).
+template <int MU, int SGN, int SPIN, class T>
+__device__ __forceinline__ Cx<T> add_hop(Cx<T> acc, Cx<T> w)
+{
+    const T s = SGN > 0 ? T(1) : T(-1);
+    if constexpr (SPIN < 2)
+        return cadd(acc, w);
+    else if constexpr (MU == 0)
+        return cadd(acc, cscale(s, ci(w)));
+    else if constexpr (MU == 1)
+        return SPIN == 2 ? cadd(acc, cscale(s, w)) : csub(acc, cscale(s, w));
+    else if constexpr (MU == 2)
+        return SPIN == 2 ? cadd(acc, cscale(s, ci(w))) : cadd(acc, cscale(s, cmi(w)));
+    else
+        return cadd(acc, cscale(s, w));
+}
+
+constexpr int kHopSites = su3i::kDslashHopSites;
+
+template <int MU, int SGN, int SP, int LP, int NT>
+__device__ __forceinline__ void hop_to_lds(const su3i::DslashArgs &a, uint32_t s, uint32_t n,
+                                           Cx<typename PrecT<SP>::T> *out)
+{
+    using T = typename PrecT<SP>::T;
+    Cx<T> p[4][3], m[9], h[2][3], w[2][3];
+    load_spinor<SP, NT & 2>(a.in, site_offset(a.gs, n), a.gs.plane, p);
+    load_link<LP, NT>(a.u[MU], site_offset(a.gl, SGN < 0 ? s : n), a.gl.plane, m);
+    project<MU, SGN>(p, h);
+    color_mul<(SGN > 0)>(m, h, w);
+#pragma unroll
+    for (int e = 0; e < 6; ++e)
+        out[e * kHopSites] = w[e / 3][e % 3];
+}
+
+// Entries (SPIN, C0 .. C0 + NC - 1) of one site: wl points at its hop 0.
+template <int SPIN, int C0, int NC, class T>
+__device__ __forceinline__ void sum_hops(const Cx<T> *wl, Cx<T> *z)
+{
+    constexpr int H = 6 * kHopSites;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const Cx<T> *q = wl + (C0 + c) * kHopSites;
+        constexpr int k01 = 3 * half_of_spin<0, SPIN>() * kHopSites;
+        constexpr int k23 = 3 * half_of_spin<2, SPIN>() * kHopSites;
+        Cx<T> acc = {T(0), T(0)};
+        acc = add_hop<3, +1, SPIN>(acc, q[0 * H + k23]);
+        acc = add_hop<0, -1, SPIN>(acc, q[1 * H + k01]);
+        acc = add_hop<0, +1, SPIN>(acc, q[2 * H + k01]);
+        acc = add_hop<1, -1, SPIN>(acc, q[3 * H + k01]);
+        acc = add_hop<1, +1, SPIN>(acc, q[4 * H + k01]);
+        acc = add_hop<2, -1, SPIN>(acc, q[5 * H + k23]);
+        acc = add_hop<2, +1, SPIN>(acc, q[6 * H + k23]);
+        z[c] = add_hop<3, -1, SPIN>(acc, q[7 * H + k23]);
+    }
+}
+
+template <int SP, int SPIN, int C0, int NC, int NT>
+__device__ __forceinline__ void sum_and_store(const su3i::DslashArgs &a, uint32_t s,
+                                              const Cx<typename PrecT<SP>::T> *wl)
+{
+    using T = typename PrecT<SP>::T;
+    Cx<T> z[NC];
+    sum_hops<SPIN, C0, NC>(wl, z);
+    RawVec<SP, 1> raw[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        narrow<SP, 1>(raw[c], 0, z[c]);
+    store_entries<SP, 1, NT, true, 3 * SPIN + C0, NC>(
+        static_cast<typename PrecT<SP>::R *>(a.out), site_offset(a.gs, s), a.gs.plane, 1, raw);
+}
+
+template <int SP, int LP, int NT>
+__global__ __launch_bounds__(8 * kHopSites) void k_dslash_hops(su3i::DslashArgs a)
+{
+    using T = typename PrecT<SP>::T;
+    // [hop][entry of the half spinor][site], in the dynamic LDS
+    extern __shared__ char occupancy_reserve[];
+    Cx<T> *wl = reinterpret_cast<Cx<T> *>(occupancy_reserve);
+    const uint32_t blk = a.xcd_remap ? (uint32_t)xcd_remap(blockIdx.x, gridDim.x)
+                                     : blockIdx.x;
+    const uint32_t l = threadIdx.x % kHopSites;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kHopSites);
+    const uint32_t s = blk * kHopSites + l;
+    const bool inside = s < (uint32_t)a.nsites;
+    if (inside) {
+        uint32_t c[4], ln[4];
+        coords(a, s, c, ln);
+        Cx<T> *out = wl + wave * 6 * kHopSites + l;
+        switch (wave) {
+        case 0: hop_to_lds<3, +1, SP, LP, NT>(a, s, bwd_site<3>(a, s, c[3], ln[3]), out); break;
+        case 1: hop_to_lds<0, -1, SP, LP, NT>(a, s, fwd_site<0>(a, s, c[0], ln[0]), out); break;
+        case 2: hop_to_lds<0, +1, SP, LP, NT>(a, s, bwd_site<0>(a, s, c[0], ln[0]), out); break;
+        case 3: hop_to_lds<1, -1, SP, LP, NT>(a, s, fwd_site<1>(a, s, c[1], ln[1]), out); break;
+        case 4: hop_to_lds<1, +1, SP, LP, NT>(a, s, bwd_site<1>(a, s, c[1], ln[1]), out); break;
+        case 5: hop_to_lds<2, -1, SP, LP, NT>(a, s, fwd_site<2>(a, s, c[2], ln[2]), out); break;
+        case 6: hop_to_lds<2, +1, SP, LP, NT>(a, s, bwd_site<2>(a, s, c[2], ln[2]), out); break;
+        default: hop_to_lds<3, -1, SP, LP, NT>(a, s, fwd_site<3>(a, s, c[3], ln[3]), out); break;
+        }
+    }
+    __syncthreads();
+    if (inside) {
+        const Cx<T> *q = wl + l;
+        switch (wave) {
+        case 0: sum_and_store<SP, 0, 0, 2, NT>(a, s, q); break;
+        case 1: sum_and_store<SP, 0, 2, 1, NT>(a, s, q); break;
+        case 2: sum_and_store<SP, 1, 0, 2, NT>(a, s, q); break;
+        case 3: sum_and_store<SP, 1, 2, 1, NT>(a, s, q); break;
+        case 4: sum_and_store<SP, 2, 0, 2, NT>(a, s, q); break;
+        case 5: sum_and_store<SP, 2, 2, 1, NT>(a, s, q); break;
+        case 6: sum_and_store<SP, 3, 0, 2, NT>(a, s, q); break;
+        default: sum_and_store<SP, 3, 2, 1, NT>(a, s, q); break;
+        }
+    }
+}
+
 // t-walk (lexicographic site order): a lane owns one (x, y, z) site and
 // walks t-slices t0 .. t1-1.
 // Along t each spinor and each t-link is loaded once per walk: at slice t
@@ -920,7 +1053,9 @@ template <int SP, int LP, int NT>
 static void go_nt(int block, int grid, size_t shm, const su3i::DslashArgs &a,
                   hipStream_t st)
 {
-    if (a.walk > 1)
+    if (a.hop_waves)
+        hipLaunchKernelGGL((k_dslash_hops<SP, LP, NT>), dim3(grid), dim3(block), shm, st, a);
+    else if (a.walk > 1)
         hipLaunchKernelGGL((k_dslash_walk<SP, LP, NT>), dim3(grid), dim3(block), shm, st, a);
     else
         hipLaunchKernelGGL((k_dslash<SP, LP, NT>), dim3(grid), dim3(block), shm, st, a);
@@ -965,6 +1100,10 @@ hipError_t launch_dslash(int spinor_prec, int link_prec, int nt, int block,
         if (!lds_shape((int)a.lds_tile, block, cbytes, (int)a.dims[0], (int)a.lmask + 1, sh) ||
             block != sh.nsub * sh.tx * sh.ty * sh.tz || (uint32_t)sh.tx != a.lds_tx ||
             shm < lds_shape_bytes(sh, cbytes))
+            return hipErrorInvalidValue;
+    } else if (a.hop_waves) {
+        const size_t cbytes = spinor_prec == F64 ? 16 : 8;
+        if (block != kDslashHopBlock || shm < kDslashHopComplex * cbytes)
             return hipErrorInvalidValue;
     } else if (block > 256) {
         return hipErrorInvalidValue;
