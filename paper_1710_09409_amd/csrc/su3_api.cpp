@@ -5,7 +5,11 @@
 
 #include <hip/hip_runtime.h>
 
+#include <sys/mman.h>
+#include <unistd.h>
+
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -15,6 +19,7 @@
 #include <array>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -249,11 +254,14 @@ extern "C" su3_status su3_spinor_bytes(const int32_t dims[4],
     return bytes_of_kind(dims, prec, layout, lanes, bytes, KIND_SPINOR);
 }
 
+static std::atomic<int64_t> g_live_fields{0};
+
 static su3_field *new_handle(const int32_t dims[4], int prec, int layout,
                              int32_t lanes, const Shape &s, int kind,
                              const int32_t *simd = nullptr)
 {
     su3_field *f = new su3_field();
+    ++g_live_fields;
     f->ptr = nullptr;
     f->bytes = s.bytes;
     std::memcpy(f->dims, dims, sizeof f->dims);
@@ -471,6 +479,8 @@ extern "C" su3_status su3_vnode_wrap(su3_field **out, void *dev_ptr,
                         kind, simd);
 }
 
+static void release_stages();
+
 extern "C" su3_status su3_field_free(su3_field *f)
 {
     if (!f)
@@ -479,6 +489,8 @@ extern "C" su3_status su3_field_free(su3_field *f)
     if (f->owns && f->ptr)
         e = hipFree(f->ptr);
     delete f;
+    if (--g_live_fields == 0)
+        release_stages();
     if (e != hipSuccess)
         return hip_fail(e, "hipFree");
     return SU3_OK;
@@ -528,18 +540,195 @@ static inline double get_real(const void *img, int prec, int64_t idx)
     return (double)static_cast<const float *>(img)[idx];
 }
 
+// Device buffers that hold a part of a field's canonical data on its way to
+// or from the host.  A transfer holds one for itself until its stream is
+// done with it; up to kStagesKept of them wait for the next transfer (any
+// thread, any stream) and go back to the device with the last field.
+struct Stage {
+    void *ptr;
+    size_t bytes;
+    int device;
+};
+static const size_t kStageBytes = (size_t)16 << 20;
+static const size_t kStagesKept = 4;
+static std::mutex g_stage_mu;
+static std::vector<Stage> g_stages;
+
+static bool acquire_stage(int device, size_t bytes, Stage *out)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_stage_mu);
+        for (size_t i = 0; i < g_stages.size(); ++i)
+            if (g_stages[i].device == device && g_stages[i].bytes >= bytes) {
+                *out = g_stages[i];
+                g_stages.erase(g_stages.begin() + (ptrdiff_t)i);
+                return true;
+            }
+    }
+    out->device = device;
+    out->bytes = bytes > (size_t)1 << 20 ? kStageBytes : (size_t)1 << 20;
+    if (hipMalloc(&out->ptr, out->bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return true;
+}
+
+static void give_back_stage(Stage s)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_stage_mu);
+        if (g_stages.size() < kStagesKept) {
+            g_stages.push_back(s);
+            return;
+        }
+        for (Stage &k : g_stages)  // keep the larger ones
+            if (k.bytes < s.bytes)
+                std::swap(k, s);
+    }
+    (void)hipFree(s.ptr);
+}
+
+static void release_stages()
+{
+    std::vector<Stage> free_now;
+    {
+        std::lock_guard<std::mutex> lk(g_stage_mu);
+        free_now.swap(g_stages);
+    }
+    for (const Stage &s : free_now)
+        (void)hipFree(s.ptr);
+}
+
+// Fields of at least this many stored reals are converted on the device
+// (below, one thread packs them in less than the extra launch takes).
+static const int64_t kDeviceConvertReals = 8192;
+
+// Run `part` over the canonical data of a field in pieces that fit a staging
+// buffer: part(order of the piece, its first host double, its bytes).
+// Returns false, with nothing run, where the device cannot convert (a small
+// field, another current device, no memory to stage in); *st is the result
+// otherwise.
+template <class F>
+static bool convert_on_device(const su3_field *f, hipStream_t hs, F part, su3_status *st)
+{
+    int dev = -1;
+    if (f->V * f->E * f->ncomp < kDeviceConvertReals || hipGetDevice(&dev) != hipSuccess ||
+        dev != f->device)
+        return false;
+    const int64_t site_doubles = (int64_t)f->canon * f->ncomp;
+    const int64_t per = std::min<int64_t>(f->V, (int64_t)(kStageBytes / 8) / site_doubles);
+    Stage stage;
+    if (!acquire_stage(dev, (size_t)(per * site_doubles) * 8, &stage))
+        return false;
+    HostOrder h;
+    std::memset(&h, 0, sizeof h);
+    h.field = f->ptr;
+    h.canon = static_cast<double *>(stage.ptr);
+    h.g = geom_of(f);
+    h.V = f->V;
+    h.Vpad = f->Vpad;
+    h.E = f->E;
+    h.canon_entries = f->canon;
+    h.ncomp = f->ncomp;
+    h.prec = f->prec;
+    h.vnode = f->layout == SU3_LAYOUT_VNODE;
+    for (int d = 0; d < 4; ++d) {
+        h.dims[d] = f->dims[d];
+        h.sub[d] = f->dims[d] / f->simd[d];
+        h.simd[d] = f->simd[d];
+    }
+    hipError_t e = hipSuccess;
+    const char *what = "";
+    for (int64_t s0 = 0; s0 < f->V && e == hipSuccess; s0 += per) {
+        h.s0 = s0;
+        h.count = std::min(per, f->V - s0);
+        e = part(h, s0 * site_doubles, (size_t)(h.count * site_doubles) * 8, &what);
+    }
+    // the buffer is free once the stream has passed its last use
+    const hipError_t sync = hipStreamSynchronize(hs);
+    give_back_stage(stage);
+    if (e == hipSuccess && sync != hipSuccess) {
+        e = sync;
+        what = "transfer sync";
+    }
+    *st = e == hipSuccess ? SU3_OK : hip_fail(e, what);
+    return true;
+}
+
+// Have the kernel map the pages of a large host buffer that is about to be
+// written (a fresh one faults on every page: 48 MB takes 11 ms from one
+// thread).  Contents stay as they are; the calling thread goes on copying
+// meanwhile.
+struct Populate {
+    std::vector<std::thread> workers;
+    std::atomic<size_t> next{0};
+
+    Populate(void *host, size_t bytes)
+    {
+#ifdef MADV_POPULATE_WRITE
+        const size_t piece = (size_t)4 << 20;
+        const size_t pieces = bytes / piece;
+        const size_t cpus = std::max(1u, std::thread::hardware_concurrency() / 2);
+        const size_t n = std::min(std::min<size_t>(8, cpus), pieces / 2);
+        const size_t page = (size_t)sysconf(_SC_PAGESIZE);
+        unsigned char *first = reinterpret_cast<unsigned char *>((uintptr_t)host / page * page);
+        unsigned char *end = static_cast<unsigned char *>(host) + bytes;
+        try {
+            for (size_t t = 0; t < n; ++t)
+                workers.emplace_back([this, first, end, piece, pieces]() {
+                    for (;;) {
+                        const size_t i = next++;
+                        if (i > pieces)
+                            return;
+                        unsigned char *p = first + i * piece;
+                        if (p >= end)
+                            return;
+                        (void)madvise(p, std::min<size_t>(piece, (size_t)(end - p)),
+                                      MADV_POPULATE_WRITE);
+                    }
+                });
+        } catch (...) {
+            // no thread to be had: the copy faults the pages itself
+        }
+#else
+        (void)host;
+        (void)bytes;
+#endif
+    }
+    ~Populate()
+    {
+        for (std::thread &t : workers)
+            t.join();
+    }
+};
+
 extern "C" su3_status su3_field_upload(su3_field *f, const double *host,
                                        void *stream)
 {
     if (!f || !host)
         return fail(SU3_ERR_INVALID_ARG, "field or host buffer is NULL");
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    su3_status done;
+    if (convert_on_device(
+            f, st,
+            [&](const HostOrder &h, int64_t first, size_t bytes, const char **what) {
+                *what = "upload copy";
+                const hipError_t e = hipMemcpyAsync(h.canon, host + first, bytes,
+                                                    hipMemcpyHostToDevice, st);
+                if (e != hipSuccess)
+                    return e;
+                *what = "upload conversion";
+                return launch_pack(h, st);
+            },
+            &done))
+        return done;
     std::vector<unsigned char> img(f->bytes, 0);
     for (int64_t s = 0; s < f->V; ++s)
         for (int e = 0; e < f->E; ++e)
             for (int c = 0; c < f->ncomp; ++c)
                 put_real(img.data(), f->prec, stored_index(f, s, e, c),
                          host[f->ncomp * (f->canon * s + e) + c]);
-    hipStream_t st = static_cast<hipStream_t>(stream);
     HIP_TRY(hipMemcpyAsync(f->ptr, img.data(), f->bytes,
                            hipMemcpyHostToDevice, st),
             "upload copy");
@@ -556,6 +745,7 @@ extern "C" su3_status su3_field_download_raw(const su3_field *f, void *host,
         return fail(SU3_ERR_INVALID_ARG, "host buffer of %zu bytes < %zu",
                     bytes, f->bytes);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    Populate pages(host, f->bytes);
     HIP_TRY(hipMemcpyAsync(host, f->ptr, f->bytes, hipMemcpyDeviceToHost, st),
             "download copy");
     HIP_TRY(hipStreamSynchronize(st), "download sync");
@@ -567,6 +757,24 @@ extern "C" su3_status su3_field_download(const su3_field *f, double *host,
 {
     if (!f || !host)
         return fail(SU3_ERR_INVALID_ARG, "field or host buffer is NULL");
+    {
+        hipStream_t hs = static_cast<hipStream_t>(stream);
+        su3_status done;
+        Populate pages(host, (size_t)(f->V * f->canon * f->ncomp) * 8);
+        if (convert_on_device(
+                f, hs,
+                [&](const HostOrder &h, int64_t first, size_t bytes, const char **what) {
+                    *what = "download conversion";
+                    const hipError_t e = launch_unpack(h, hs);
+                    if (e != hipSuccess)
+                        return e;
+                    *what = "download copy";
+                    return hipMemcpyAsync(host + first, h.canon, bytes,
+                                          hipMemcpyDeviceToHost, hs);
+                },
+                &done))
+            return done;
+    }
     std::vector<unsigned char> img(f->bytes);
     su3_status st = su3_field_download_raw(f, img.data(), img.size(), stream);
     if (st != SU3_OK)

@@ -137,6 +137,23 @@ struct ItemChunk {
 // zero the ticket counter *queue.
 hipError_t launch_put_items(BatchItem *dst, const BatchItem *items, int n,
                             unsigned long long *queue, hipStream_t stream);
+// Host data of a field as the caller holds it: canon entries of ncomp
+// doubles per lattice site, E of them stored (the two-row form stores 6 of
+// 9), converted to and from the stored order on the device.  The canonical
+// buffer holds the sites s0 .. s0 + count - 1 of V.  Packing also writes
+// zeros to the padding sites V .. Vpad - 1 when the range ends at V.
+struct HostOrder {
+    void *field;        // stored reals
+    double *canon;      // device copy of the canonical range
+    Geom g;
+    int64_t s0, count, V, Vpad;
+    int32_t E, canon_entries, ncomp, prec;
+    // virtual-node layout (vnode != 0): lattice extents, sub-lattice extents
+    // and node counts per direction
+    int32_t vnode, dims[4], sub[4], simd[4];
+};
+hipError_t launch_pack(const HostOrder &h, hipStream_t stream);
+hipError_t launch_unpack(const HostOrder &h, hipStream_t stream);
 // Bandwidth yardsticks over n16 16-byte elements per array (kinds below);
 // `tail` adds the triad's trailing double; nt in {0, 1, 2, 3, 6, 7};
 // block a multiple of 64 up to 1024; `shm` as for launch_site.

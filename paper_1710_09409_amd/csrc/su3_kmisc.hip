@@ -159,6 +159,103 @@ __global__ __launch_bounds__(64) void k_put_items(BatchItem *dst, su3i::ItemChun
         *queue = 0ull;
 }
 
+// Stored order <-> canonical host order.  A workgroup handles 64 sites, one
+// wave per entry: every wave's access to the stored field is whole lines,
+// and the 64 sites' canonical records (9 KB for a matrix), which the waves
+// read or write with a stride, stay in the L1 for all of them.  The kernels
+// run behind the PCIe copies of the canonical data (48 MB: 1.6 ms) and take
+// a few per cent of their time.
+__device__ __forceinline__ uint32_t storage_of(const su3i::HostOrder &h, uint32_t s)
+{
+    if (!h.vnode)
+        return s;
+    uint32_t osite = 0, lane = 0, ostride = 1, lstride = 1;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t x = s % (uint32_t)h.dims[d];
+        s /= (uint32_t)h.dims[d];
+        const uint32_t n = x / (uint32_t)h.sub[d];
+        osite += (x - n * h.sub[d]) * ostride;
+        lane += n * lstride;
+        ostride *= h.sub[d];
+        lstride *= h.simd[d];
+    }
+    return osite * lstride + lane;
+}
+
+// Offset (stored reals) of entry e of storage site q; real scalars hold one
+// real per entry, so their offsets are half of a complex entry's.
+__device__ __forceinline__ uint32_t entry_offset(const su3i::HostOrder &h, uint32_t q, int e)
+{
+    return h.ncomp == 1 ? q : site_offset(h.g, q) + (uint32_t)e * h.g.plane;
+}
+
+__device__ __forceinline__ void put_stored(const su3i::HostOrder &h, uint32_t at, double v)
+{
+    if (h.prec == su3i::F64) {
+        static_cast<double *>(h.field)[at] = v;
+    } else {
+        // to half by way of single, each rounding to nearest even (the empty
+        // asm keeps the two conversions apart)
+        float f = (float)v;
+        __asm__ volatile("" : "+v"(f));
+        if (h.prec == su3i::F16)
+            static_cast<_Float16 *>(h.field)[at] = (_Float16)f;
+        else
+            static_cast<float *>(h.field)[at] = f;
+    }
+}
+
+__device__ __forceinline__ double get_stored(const su3i::HostOrder &h, uint32_t at)
+{
+    if (h.prec == su3i::F64)
+        return static_cast<const double *>(h.field)[at];
+    if (h.prec == su3i::F16)
+        return (double)(float)static_cast<const _Float16 *>(h.field)[at];
+    return (double)static_cast<const float *>(h.field)[at];
+}
+
+__global__ __launch_bounds__(768) void k_pack(su3i::HostOrder h)
+{
+    const int e = threadIdx.x / 64;
+    const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x % 64;  // in the range
+    const int64_t s = h.s0 + i;
+    const bool site = i < h.count, pad = !site && s >= h.V && s < h.Vpad;
+    if (!site && !pad)
+        return;
+    const uint32_t at = entry_offset(h, site ? storage_of(h, (uint32_t)s) : (uint32_t)s, e);
+    const double *v = h.canon + (i * h.canon_entries + e) * h.ncomp;
+    for (int c = 0; c < h.ncomp; ++c)
+        put_stored(h, at + c, site ? v[c] : 0.0);
+}
+
+__global__ __launch_bounds__(768) void k_unpack(su3i::HostOrder h)
+{
+    const int e = threadIdx.x / 64;
+    const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x % 64;
+    if (i >= h.count)
+        return;
+    const uint32_t q = storage_of(h, (uint32_t)(h.s0 + i));
+    double *v = h.canon + (i * h.canon_entries + e) * h.ncomp;
+    if (e < h.E) {
+        const uint32_t at = entry_offset(h, q, e);
+        for (int c = 0; c < h.ncomp; ++c)
+            v[c] = get_stored(h, at + c);
+        return;
+    }
+    // row 2 of the two-row form: conj(row0 x row1) of the stored single
+    // values, whose products are exact in double
+    const int k = e - 6, p0 = (k + 1) % 3, q0 = (k + 2) % 3;
+    const uint32_t a = entry_offset(h, q, p0), b = entry_offset(h, q, 3 + q0);
+    const uint32_t c = entry_offset(h, q, q0), d = entry_offset(h, q, 3 + p0);
+    const double ar = get_stored(h, a), ai = get_stored(h, a + 1);
+    const double br = get_stored(h, b), bi = get_stored(h, b + 1);
+    const double cr = get_stored(h, c), ci = get_stored(h, c + 1);
+    const double dr = get_stored(h, d), di = get_stored(h, d + 1);
+    v[0] = (ar * br - ai * bi) - (cr * dr - ci * di);
+    v[1] = -((ar * bi + ai * br) - (cr * di + ci * dr));
+}
+
 // Bandwidth yardsticks, one 16-byte element per lane, one-shot grid:
 // triad a = b + s*c (doubles), read-only (b and c), write-only (a = s),
 // copy (a = b).  The read-only kind writes a[0] only if an element of
@@ -300,6 +397,31 @@ hipError_t launch_put_items(BatchItem *dst, const BatchItem *items, int n,
             return e;
     }
     return hipSuccess;
+}
+
+static bool host_order_ok(const HostOrder &h)
+{
+    return h.count > 0 && h.s0 >= 0 && h.s0 + h.count <= h.V && h.E >= 1 &&
+           h.canon_entries <= 12 && h.E <= h.canon_entries;
+}
+
+hipError_t launch_pack(const HostOrder &h, hipStream_t st)
+{
+    if (!host_order_ok(h))
+        return hipErrorInvalidValue;
+    const int64_t sites = h.s0 + h.count == h.V ? h.Vpad - h.s0 : h.count;
+    hipLaunchKernelGGL(su3k::k_pack, dim3((unsigned)((sites + 63) / 64)), dim3(64 * h.E), 0, st,
+                       h);
+    return hipGetLastError();
+}
+
+hipError_t launch_unpack(const HostOrder &h, hipStream_t st)
+{
+    if (!host_order_ok(h))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(su3k::k_unpack, dim3((unsigned)((h.count + 63) / 64)),
+                       dim3(64 * h.canon_entries), 0, st, h);
+    return hipGetLastError();
 }
 
 template <int KIND, int NT>
