@@ -1794,6 +1794,82 @@ extern "C" su3_status su3_program_destroy(su3_program *p)
     return SU3_OK;
 }
 
+// The row form takes matrix programs on three waves, which meet at barriers.
+// A host build of this library runs a kernel's lanes one after another, where
+// only the larger lattices may take it.
+#ifdef __HIP__
+static const int64_t kProgRowsSites = 1;
+#else
+static const int64_t kProgRowsSites = 2048;
+#endif
+
+static int row_sites_per_lane(const su3_field *z, int arith)
+{
+    return arith == SU3_F32 && z->L % 2 == 0 ? 2 : 1;
+}
+
+// The code of a matrix program in the row form, or null for the one-lane
+// kernel.
+static const RowCode *row_code(const su3_program *p, const su3_field *z, int arith)
+{
+    const ProgCode &pc = p->code;
+    const bool aos = z->layout == SU3_LAYOUT_AOS;
+    if (pc.rows.n == 0 || z->V < kProgRowsSites)
+        return nullptr;
+    // AoS matrices without a matrix to store: the one-lane kernel's cached
+    // loads reach the rest of a site's record in the same lines (FP64 32^4
+    // trace(a*adj(b)): 58 us against 88 through LDS); with one, its stores of
+    // 16 bytes per record cost more (a*adj(b): 368 us against 101).
+    if (aos && pc.result_kind != FK_MATRIX)
+        return nullptr;
+    const DeviceFacts f = device_facts(z->device);
+    const int spl = row_sites_per_lane(z, arith);
+    const int64_t groups = (z->V + 64 * spl - 1) / (64 * spl);
+    const int64_t slots = (int64_t)pc.rows.nslots * kRowSlotVecs * spl * 2 * real_bytes(arith);
+    // every workgroup resident at once: nothing to gain from smaller ones
+    // (force term, six slots, FP64 12^4: 12.1 us, with registers 14.3)
+    if (groups <= f.cus * (f.lds_per_cu / slots))
+        return &pc.rows;
+    // Up to four slots of 9 KB the registers cost more than the waves they
+    // make room for (FP64 48^4 a*b+c*d: 630 us, with registers 646); beyond,
+    // values that stay with their wave move there (force term FP64 48^4: 1679
+    // us in slots, 1090 with registers, 1437 on the one-lane kernel; FP32 855,
+    // 517 and 560).
+    if (pc.rows.nslots > 4)
+        return aos ? &pc.rows_aos : &pc.rows_held;
+    // Four slots: 12 waves per CU with the loads of 16 bytes per lane and row
+    // are too few in single (FP32 20^4 a*b+c*d: 14.7 us against 11.5 on the
+    // one-lane kernel, 48^4 trace(a*b*adj(c)*adj(d)) 283 against 259).
+    if (pc.rows.nslots == 4 && arith == SU3_F32 && !aos)
+        return nullptr;
+    return &pc.rows;
+}
+
+// The launch of a matrix program that nothing tuned or set (rows: its row
+// form).  Loads stay cached in calls that the Infinity Cache holds with the
+// fields in use around them (FP32 24^4 a*adj(b), 72 MB: 12.9 us against 14.3),
+// where a lane-block's entry is less than a 128-byte line (FP32 AoSoA-8 32^4
+// a*b+c*d: 66.6 us against 72.9), and for AoS sites read entry by entry.  One
+// product alone streams best with 5 workgroups per CU (FP64 48^4 a*adj(b):
+// 361 us, uncapped 405); longer programs want them all.
+static su3_launch program_launch(const su3_program *p, const su3_field *z,
+                                 const su3_field *const *ops, int arith, const RowCode *rows,
+                                 su3_expr key)
+{
+    su3_launch c = default_launch(key, arith, z->layout, z->V);
+    int64_t bytes = (int64_t)z->bytes;
+    for (int k = 0; k < p->code.nops; ++k)
+        if (p->code.used >> k & 1)
+            bytes += (int64_t)ops[k]->bytes;
+    const int64_t MB = 1000 * 1000;
+    const bool aos = z->layout == SU3_LAYOUT_AOS;
+    const bool split = aos ? !rows : z->L * 2 * (int64_t)real_bytes(arith) < 128;
+    c.nontemporal = bytes <= 150 * MB || split ? 2 : 3;
+    if (rows && rows->n == 1 && bytes > 256 * MB && !aos)
+        c.occupancy = 5;
+    return c;
+}
+
 static su3_status launch_program_op(const su3_program *p, su3_field *z,
                                     const su3_field *const *ops, int arith,
                                     hipStream_t st,
@@ -1807,8 +1883,13 @@ static su3_status launch_program_op(const su3_program *p, su3_field *z,
     const su3_expr key = form == PF_MATRIX && p->code.result_kind != FK_MATRIX
                              ? SU3_EXPR_PROGRAM_SCALAR
                              : SU3_EXPR_PROGRAM;
-    su3_launch c =
-        forced ? *forced : lookup_launch(key, arith, z->layout, z->lanes, z->V);
+    const RowCode *rows = form == PF_MATRIX ? row_code(p, z, arith) : nullptr;
+    su3_launch c;
+    if (forced)
+        c = *forced;
+    else if (!tuned_launch(key, arith, z->layout, z->lanes, z->V, &c))
+        c = form == PF_MATRIX ? program_launch(p, z, ops, arith, rows, key)
+                              : default_launch(key, arith, z->layout, z->V);
     if (!forced && form != PF_MATRIX) {
         // the block and occupancy cap are the matrix kernel's (a wave of it
         // keeps up to 18 KB of loads in flight); a scalar-valued wave keeps
@@ -1839,10 +1920,38 @@ static su3_status launch_program_op(const su3_program *p, su3_field *z,
         a.imm[k][0] = p->code.imm[k][0];
         a.imm[k][1] = p->code.imm[k][1];
     }
+    hipError_t e;
+    if (rows) {
+        RowArgs r;
+        std::memset(&r, 0, sizeof r);
+        r.z = a.z;
+        r.gz = a.gz;
+        r.zkind = a.zkind;
+        r.zprec = a.zprec;
+        std::memcpy(r.op, a.op, sizeof r.op);
+        std::memcpy(r.g, a.g, sizeof r.g);
+        std::memcpy(r.kind, a.kind, sizeof r.kind);
+        std::memcpy(r.prec, a.prec, sizeof r.prec);
+        std::memcpy(r.slot, rows->slot, sizeof r.slot);
+        std::memcpy(r.imm, a.imm, sizeof r.imm);
+        std::memcpy(r.ins, rows->ins, sizeof r.ins);
+        r.nops = a.nops;
+        r.used = a.used;
+        r.ninstr = (uint8_t)rows->n;
+        r.nslots = (uint8_t)rows->nslots;
+        r.held = rows->held;
+        r.aos = z->layout == SU3_LAYOUT_AOS;
+        r.nsites = a.nsites;
+        e = launch_program_rows(arith, row_sites_per_lane(z, arith), c.nontemporal,
+                                occupancy_reserve(z->device, c.occupancy), r, st);
+        if (e != hipSuccess)
+            return hip_fail(e, "program kernel launch");
+        return SU3_OK;
+    }
     const int64_t per = program_sites_per_lane(arith, form);
     const int64_t lanes = (z->V + per - 1) / per;
     const int64_t grid = (lanes + c.block - 1) / c.block;
-    hipError_t e = launch_program(arith, form, p->code.nregs,
+    e = launch_program(arith, form, p->code.nregs,
                                   c.nontemporal, c.block, (int)grid,
                                   occupancy_reserve(z->device, c.occupancy), a,
                                   st);

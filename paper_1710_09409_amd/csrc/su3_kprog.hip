@@ -451,6 +451,543 @@ __global__ __launch_bounds__(256) void k_program(ProgArgs a)
         occupancy_reserve[threadIdx.x] = 0;
 }
 
+// ------------------------------------------- matrix programs, row by row
+//
+// The row form (su3_program.h): three waves of a workgroup hold the three
+// rows of every matrix value of 64 lanes' sites (S per lane: 16 bytes per
+// entry and lane), wave r the row r.  Values live in LDS slots of 9 entries,
+// so an instruction's operand is an address -- no selection of registers by
+// chains of branches and copies, which cost the one-lane interpreter more
+// than its arithmetic -- and a lane needs registers for a few rows only: the
+// waves a CU holds are set by the slots a program needs (9.1 KiB each), 24
+// for two slots, 6 for seven, against 4 in double for the one-lane kernel.
+// The last result is also in the accumulator Z.  A product reads its right
+// operand's rows, a transposed operand its columns and a trace its diagonal
+// from the slots the other waves wrote; the host sets the barriers that need
+// (before a read of rows written since the last barrier, before a write of a
+// slot read by other waves since then).  A scalar is computed by all three
+// waves, each with a copy of its own in the slot.  Entries are summed as in
+// the one-lane kernel: the same bits.
+constexpr int kRowLanes = 64;  // lanes per row: a wave
+// Vectors from one entry to the next: an odd count, so that whole AoS
+// records (entries side by side) go into a slot without bank conflicts.
+constexpr int kRowEntry = kRowLanes + 1;
+constexpr int kRowSlot = 9 * kRowEntry;
+static_assert(kRowSlot == su3i::kRowSlotVecs, "the host sizes LDS by it");
+
+template <class T, int S>
+struct RowVal {
+    Cx<T> m[3][S];
+};
+
+// Forms of the kernel, or'ed.
+enum RowForm {
+    ROWF_HELD = 1,  // the code uses registers
+    ROWF_AOS = 2,   // operands and result pass through LDS as whole records
+};
+
+template <class T, int S>
+struct RowFrame {
+    using V = typename VecOf<T, 2 * S>::type;
+    V *own;  // entry (row, 0) of this lane's sites in slot 0
+    V *all;  // entry (0, 0)
+    int row;
+    RowVal<T, S> Z, W0, W1;  // accumulator, registers
+};
+
+static_assert(su3i::kRowRegisters == 2, "held() and hold() name them");
+
+template <bool HELD, class T, int S>
+__device__ __forceinline__ RowVal<T, S> held(int src, const RowFrame<T, S> &f)
+{
+    if constexpr (!HELD)
+        return f.Z;
+    const bool z = src == su3i::ROW_ACC, w = src == su3i::ROW_ACC + 1;
+    RowVal<T, S> x;
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const Cx<T> zv = f.Z.m[j][q], wv = f.W0.m[j][q], vv = f.W1.m[j][q];
+            x.m[j][q] = {z ? zv.re : w ? wv.re : vv.re, z ? zv.im : w ? wv.im : vv.im};
+        }
+    return x;
+}
+
+template <class T, int S>
+__device__ __forceinline__ void hold(int d, const RowVal<T, S> &x, RowFrame<T, S> &f)
+{
+    const bool w = d == su3i::ROW_ACC + 1;
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const Cx<T> v = x.m[j][q], w0 = f.W0.m[j][q], w1 = f.W1.m[j][q];
+            f.W0.m[j][q] = {w ? v.re : w0.re, w ? v.im : w0.im};
+            f.W1.m[j][q] = {w ? w1.re : v.re, w ? w1.im : v.im};
+        }
+}
+
+template <class T, int S>
+__device__ __forceinline__ void unpack(const typename VecOf<T, 2 * S>::type &v, Cx<T> (&c)[S])
+{
+#pragma unroll
+    for (int q = 0; q < S; ++q)
+        c[q] = {v[2 * q], v[2 * q + 1]};
+}
+
+template <class T, int S>
+__device__ __forceinline__ typename VecOf<T, 2 * S>::type pack(const Cx<T> (&c)[S])
+{
+    typename VecOf<T, 2 * S>::type v;
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+        v[2 * q] = c[q].re;
+        v[2 * q + 1] = c[q].im;
+    }
+    return v;
+}
+
+template <int N, class T, int S>
+__device__ __forceinline__ void apply_mode(int mode, RowVal<T, S> &x)
+{
+    if (mode & su3i::ROW_CONJ) {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                x.m[j][q].im = -x.m[j][q].im;
+    }
+    if (mode & su3i::ROW_NEG) {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                x.m[j][q] = {-x.m[j][q].re, -x.m[j][q].im};
+    }
+}
+
+// This wave's row of a matrix source.
+template <bool HELD, class T, int S>
+__device__ __forceinline__ RowVal<T, S> row_of(int src, int mode, const RowFrame<T, S> &f)
+{
+    RowVal<T, S> x;
+    if (src & su3i::ROW_ACC) {
+        x = held<HELD>(src, f);
+    } else if (mode & su3i::ROW_TRANS) {
+        const auto *p = f.all + src * kRowSlot + f.row * kRowEntry;
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            unpack<T, S>(p[3 * j * kRowEntry], x.m[j]);
+    } else {
+        const auto *p = f.own + src * kRowSlot;
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            unpack<T, S>(p[j * kRowEntry], x.m[j]);
+    }
+    apply_mode<3>(mode, x);
+    return x;
+}
+
+// A scalar source, in x.m[0] (this wave's copy: entry (row, 0)).
+template <bool HELD, class T, int S>
+__device__ __forceinline__ RowVal<T, S> scalar_of(int src, int mode, const su3i::RowArgs &a,
+                                                  const RowFrame<T, S> &f)
+{
+    RowVal<T, S> x;
+    if (src & su3i::ROW_ACC) {
+        x = held<HELD>(src, f);
+    } else if (src & su3i::ROW_IMM) {
+        const int k = src & 7;
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+            x.m[0][q] = {T(a.imm[k][0]), T(a.imm[k][1])};
+    } else {
+        unpack<T, S>(f.own[src * kRowSlot], x.m[0]);
+    }
+    apply_mode<1>(mode, x);
+    return x;
+}
+
+// Row of A * B, entry (k, j) of B at b[k * SK + j * SJ]; each entry is
+// summed over k as in mat_mul.
+template <int SK, int SJ, class T, int S>
+__device__ __forceinline__ void row_product(const RowVal<T, S> &A,
+                                            const typename VecOf<T, 2 * S>::type *b, bool conj,
+                                            RowVal<T, S> &z)
+{
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        RowVal<T, S> e;
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            unpack<T, S>(b[k * SK + j * SJ], e.m[j]);
+        if (conj)
+            apply_mode<3>(su3i::ROW_CONJ, e);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const Cx<T> x = A.m[k][q], y = e.m[j][q];
+                Cx<T> &c = z.m[j][q];
+                if (k == 0) {
+                    c.re = x.re * y.re;
+                    c.im = x.re * y.im;
+                } else {
+                    c.re = fma_t(x.re, y.re, c.re);
+                }
+                c.re = fma_t(-x.im, y.im, c.re);
+                if (k != 0)
+                    c.im = fma_t(x.re, y.im, c.im);
+                c.im = fma_t(x.im, y.re, c.im);
+            }
+    }
+}
+
+// Row f.row of operand k (or the scalar) of the S sites from s0 into its
+// slot's registers.  Loads are whole vectors: fields are padded to whole
+// lane-blocks of a multiple of S.
+template <int P, int S, int NT>
+__device__ __forceinline__ void load_row(const void *base, const su3i::Geom &g, uint32_t s0,
+                                         int row, RowVal<typename PrecT<P>::T, S> &r)
+{
+    using R = typename PrecT<P>::R;
+    const R *p = static_cast<const R *>(base);
+    const uint32_t off = site_offset(g, s0);
+    if (P == su3i::C12 && row == 2) {  // rebuilt from rows 0 and 1
+        RawVec<P, S> raw[6];
+        load_entries<P, S, NT, true, 0, 6>(p, off, g.plane, S, raw);
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            Cx<typename PrecT<P>::T> m[9];
+#pragma unroll
+            for (int e = 0; e < 6; ++e)
+                m[e] = widen<P, S>(raw[e], q);
+            rebuild_row2(m);
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                r.m[j][q] = m[6 + j];
+        }
+    } else {
+        RawVec<P, S> raw[3];
+        load_entries<P, S, NT, true, 0, 3>(p, off + 3 * row * g.plane, g.plane, S, raw);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                r.m[j][q] = widen<P, S>(raw[j], q);
+    }
+}
+
+template <class T, int S, int NT>
+__device__ __forceinline__ void load_row_operand(const su3i::RowArgs &a, int k, uint32_t s0,
+                                                 int row, RowVal<T, S> &r)
+{
+    const void *base = a.op[k];
+    if (a.kind[k] == su3i::FK_MATRIX) {
+        if constexpr (sizeof(T) == 8)
+            load_row<su3i::F64, S, NT>(base, a.g[k], s0, row, r);
+        else if (a.prec[k] == su3i::C12)
+            load_row<su3i::C12, S, NT>(base, a.g[k], s0, row, r);
+        else
+            load_row<su3i::F32, S, NT>(base, a.g[k], s0, row, r);
+    } else if (a.kind[k] == su3i::FK_REAL) {
+        const T *p = static_cast<const T *>(base) + s0;
+        if constexpr (S == 1) {
+            r.m[0][0] = {vload<NT & 1>(p), T(0)};
+        } else {
+            using V = typename VecOf<T, S>::type;
+            const V v = vload<NT & 1>(reinterpret_cast<const V *>(p));
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                r.m[0][q] = {v[q], T(0)};
+        }
+    } else {
+        using V = typename VecOf<T, 2 * S>::type;
+        unpack<T, S>(vload<NT & 1>(reinterpret_cast<const V *>(static_cast<const T *>(base) +
+                                                               2 * s0)),
+                     r.m[0]);
+    }
+}
+
+// The operands into their slots, four at a time (their loads in flight
+// together).
+template <int FORM, class T, int S, int NT>
+__device__ __forceinline__ void load_slots(const su3i::RowArgs &a, uint32_t s0, bool inside,
+                                           RowFrame<T, S> &f)
+{
+    for (int k0 = 0; k0 < a.nops; k0 += 4) {
+        RowVal<T, S> v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (inside && k0 + i < a.nops && ((a.used >> (k0 + i)) & 1))
+                load_row_operand<T, S, NT>(a, k0 + i, s0, f.row, v[i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (inside && k0 + i < a.nops && ((a.used >> (k0 + i)) & 1)) {
+                if ((FORM & ROWF_HELD) && (a.slot[k0 + i] & su3i::ROW_ACC)) {
+                    hold(a.slot[k0 + i], v[i], f);
+                    continue;
+                }
+                auto *p = f.own + a.slot[k0 + i] * kRowSlot;
+                p[0] = pack<T, S>(v[i].m[0]);
+                if (a.kind[k0 + i] == su3i::FK_MATRIX) {
+                    p[kRowEntry] = pack<T, S>(v[i].m[1]);
+                    p[2 * kRowEntry] = pack<T, S>(v[i].m[2]);
+                }
+            }
+    }
+}
+
+// AoS operands: the workgroup's 64 sites are 576 consecutive entries of each
+// matrix, read as they lie and put in place by entry and site; the rest (two-
+// row matrices, scalars) as above.
+template <class T, int NT>
+__device__ __forceinline__ void load_slots_aos(const su3i::RowArgs &a, uint32_t first,
+                                               bool inside, int lane, const RowFrame<T, 1> &f)
+{
+    using V = typename VecOf<T, 2>::type;
+    constexpr int kVecs = 9 * kRowLanes, kThreads = 3 * kRowLanes;
+    V *const slots = f.all - lane;
+    const uint32_t nvec = 9u * (uint32_t)a.nsites;
+    const uint32_t t = (uint32_t)f.row * kRowLanes + lane;
+    for (int k = 0; k < a.nops; ++k) {
+        if (!((a.used >> k) & 1))
+            continue;
+        if (a.kind[k] != su3i::FK_MATRIX || a.prec[k] == su3i::C12) {
+            if (inside) {
+                RowVal<T, 1> r;
+                load_row_operand<T, 1, NT>(a, k, first + lane, f.row, r);
+                V *p = f.own + a.slot[k] * kRowSlot;
+                p[0] = pack<T, 1>(r.m[0]);
+                if (a.kind[k] == su3i::FK_MATRIX) {
+                    p[kRowEntry] = pack<T, 1>(r.m[1]);
+                    p[2 * kRowEntry] = pack<T, 1>(r.m[2]);
+                }
+            }
+            continue;
+        }
+        const V *g = static_cast<const V *>(a.op[k]);
+        V v[kVecs / kThreads];
+#pragma unroll
+        for (int i = 0; i < kVecs / kThreads; ++i) {
+            const uint32_t at = 9u * first + t + i * kThreads;
+            if (at < nvec)
+                v[i] = vload<NT & 1>(g + at);
+        }
+#pragma unroll
+        for (int i = 0; i < kVecs / kThreads; ++i) {
+            const uint32_t e = t + i * kThreads;
+            if (9u * first + e < nvec)
+                slots[a.slot[k] * kRowSlot + (e % 9) * kRowEntry + e / 9] = v[i];
+        }
+    }
+    __syncthreads();  // rows were written by every wave
+}
+
+// Row `row` of a matrix result in storage precision P (cnt of the S sites).
+template <int P, int S, int NT>
+__device__ __forceinline__ void store_row(const su3i::RowArgs &a, uint32_t s0, int row, int cnt,
+                                          const RowVal<typename PrecT<P>::T, S> &Z)
+{
+    using R = typename PrecT<P>::R;
+    RawVec<P, S> raw[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+            narrow<P, S>(raw[j], q, Z.m[j][q]);
+    const uint32_t off = site_offset(a.gz, s0) + 3 * row * a.gz.plane;
+    if (cnt >= S)
+        store_entries<P, S, NT, true, 0, 3>(static_cast<R *>(a.z), off, a.gz.plane, S, raw);
+    else
+        store_entries<P, S, NT, false, 0, 3>(static_cast<R *>(a.z), off, a.gz.plane, cnt, raw);
+}
+
+template <class T, int S, int NT, int FORM>
+__global__ __launch_bounds__(3 * kRowLanes) void k_program_rows(su3i::RowArgs a)
+{
+    extern __shared__ char occupancy_reserve[];
+    constexpr bool HELD = FORM & ROWF_HELD, AOS = FORM & ROWF_AOS;
+    using V = typename RowFrame<T, S>::V;
+    V *const slots = reinterpret_cast<V *>(occupancy_reserve);
+    const int row = __builtin_amdgcn_readfirstlane(threadIdx.x / kRowLanes);
+    const int lane = threadIdx.x % kRowLanes;
+    RowFrame<T, S> f;
+    f.own = slots + 3 * row * kRowEntry + lane;
+    f.all = slots + lane;
+    f.row = row;
+    const uint32_t first = blockIdx.x * (kRowLanes * S);  // the workgroup's first site
+    const uint32_t s0 = first + lane * S;
+    const bool inside = s0 < (uint32_t)a.nsites;  // lanes past the end only take part
+    if constexpr (AOS)
+        load_slots_aos<T, NT>(a, first, inside, lane, f);
+    else
+        load_slots<FORM, T, S, NT>(a, s0, inside, f);
+    RowVal<T, S> &Z = f.Z;
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+            Z.m[j][q] = {T(0), T(0)};
+    su3i::RowInstr next = a.ins[0];
+    for (int pc = 0; pc < a.ninstr; ++pc) {
+        const su3i::RowInstr in = next;
+        next = a.ins[pc + 1 < a.ninstr ? pc + 1 : pc];
+        if (in.flags & su3i::ROW_SYNC_READ)
+            __syncthreads();
+        switch (in.op) {
+        case su3i::ROW_MUL_M: {
+            const RowVal<T, S> A = row_of<HELD>(in.a, in.am, f);
+            const V *b = f.all + in.b * kRowSlot;
+            const bool conj = in.bm & su3i::ROW_CONJ;
+            if (in.bm & su3i::ROW_TRANS)
+                row_product<kRowEntry, 3 * kRowEntry>(A, b, conj, Z);
+            else
+                row_product<3 * kRowEntry, kRowEntry>(A, b, conj, Z);
+            break;
+        }
+        case su3i::ROW_ADD_M: {
+            const RowVal<T, S> A = row_of<HELD>(in.a, in.am, f);
+            const RowVal<T, S> B = row_of<HELD>(in.b, in.bm, f);
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int q = 0; q < S; ++q)
+                    Z.m[j][q] = {A.m[j][q].re + B.m[j][q].re, A.m[j][q].im + B.m[j][q].im};
+            break;
+        }
+        case su3i::ROW_MOV_M: Z = row_of<HELD>(in.a, in.am, f); break;
+        case su3i::ROW_MUL_SM: {
+            const RowVal<T, S> A = scalar_of<HELD>(in.a, in.am, a, f);
+            const RowVal<T, S> B = row_of<HELD>(in.b, in.bm, f);
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int q = 0; q < S; ++q)
+                    Z.m[j][q] = cmul(A.m[0][q], B.m[j][q]);
+            break;
+        }
+        case su3i::ROW_MUL_MS: {
+            const RowVal<T, S> A = row_of<HELD>(in.a, in.am, f);
+            const RowVal<T, S> B = scalar_of<HELD>(in.b, in.bm, a, f);
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int q = 0; q < S; ++q)
+                    Z.m[j][q] = cmul(A.m[j][q], B.m[0][q]);
+            break;
+        }
+        case su3i::ROW_ADD_MS: {
+            const RowVal<T, S> B = scalar_of<HELD>(in.b, in.bm, a, f);
+            Z = row_of<HELD>(in.a, in.am, f);
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (j == row)
+#pragma unroll
+                    for (int q = 0; q < S; ++q)
+                        Z.m[j][q] = {Z.m[j][q].re + B.m[0][q].re,
+                                     Z.m[j][q].im + B.m[0][q].im};
+            break;
+        }
+        case su3i::ROW_TRACE: {
+            const V *p = f.all + in.a * kRowSlot;
+            RowVal<T, S> d;
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                unpack<T, S>(p[4 * j * kRowEntry], d.m[j]);
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                Z.m[0][q] = {(d.m[0][q].re + d.m[1][q].re) + d.m[2][q].re,
+                             (d.m[0][q].im + d.m[1][q].im) + d.m[2][q].im};
+            break;
+        }
+        default: {  // scalars
+            const RowVal<T, S> A = scalar_of<HELD>(in.a, in.am, a, f);
+            if (in.op == su3i::ROW_ADD_S || in.op == su3i::ROW_MUL_S) {
+                const RowVal<T, S> B = scalar_of<HELD>(in.b, in.bm, a, f);
+#pragma unroll
+                for (int q = 0; q < S; ++q)
+                    Z.m[0][q] = in.op == su3i::ROW_MUL_S
+                                    ? cmul(A.m[0][q], B.m[0][q])
+                                    : Cx<T>{A.m[0][q].re + B.m[0][q].re,
+                                            A.m[0][q].im + B.m[0][q].im};
+            } else {
+#pragma unroll
+                for (int q = 0; q < S; ++q)
+                    Z.m[0][q] = in.op == su3i::ROW_REAL   ? Cx<T>{A.m[0][q].re, T(0)}
+                                : in.op == su3i::ROW_IMAG ? Cx<T>{A.m[0][q].im, T(0)}
+                                                          : A.m[0][q];
+            }
+            break;
+        }
+        }
+        if (in.d & su3i::ROW_ACC) {
+            if constexpr (HELD)
+                if (in.d != su3i::ROW_NONE)
+                    hold(in.d, Z, f);
+        } else {
+            if (in.flags & su3i::ROW_SYNC_WRITE)
+                __syncthreads();
+            V *p = f.own + in.d * kRowSlot;
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                p[j * kRowEntry] = pack<T, S>(Z.m[j]);
+        }
+    }
+    if constexpr (AOS) {
+        if (a.zkind == su3i::FK_MATRIX && a.zprec != su3i::C12) {
+            // the rows back through a slot, out as whole vectors
+            constexpr int kThreads = 3 * kRowLanes;
+            const uint32_t nvec = 9u * (uint32_t)a.nsites, t = threadIdx.x;
+            __syncthreads();  // every wave is done with slot 0
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                f.own[j * kRowEntry] = pack<T, 1>(Z.m[j]);
+            __syncthreads();
+            V *g = static_cast<V *>(a.z);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const uint32_t e = t + i * kThreads;
+                if (9u * first + e < nvec)
+                    vstore<NT & 2>(g + 9u * first + e, slots[(e % 9) * kRowEntry + e / 9]);
+            }
+            return;
+        }
+    }
+    if (!inside)
+        return;
+    const int left = a.nsites - (int)s0, cnt = left < S ? left : S;
+    if (a.zkind == su3i::FK_MATRIX) {
+        if constexpr (sizeof(T) == 8) {
+            store_row<su3i::F64, S, NT>(a, s0, row, cnt, Z);
+        } else if (a.zprec == su3i::C12) {
+            if (row < 2)
+                store_row<su3i::C12, S, NT>(a, s0, row, cnt, Z);
+        } else {
+            store_row<su3i::F32, S, NT>(a, s0, row, cnt, Z);
+        }
+    } else if (row == 0) {
+        T *z = static_cast<T *>(a.z);
+        if (a.zkind == su3i::FK_REAL) {
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                if (q < cnt)
+                    vstore<NT & 2>(z + s0 + q, Z.m[0][q].re);
+        } else {
+            using V2 = typename VecOf<T, 2>::type;
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                if (q < cnt) {
+                    V2 v;
+                    v[0] = Z.m[0][q].re;
+                    v[1] = Z.m[0][q].im;
+                    vstore<NT & 2>(reinterpret_cast<V2 *>(z) + s0 + q, v);
+                }
+        }
+    }
+}
+
 // Scalar-only programs: each lane evaluates S consecutive sites (one
 // complex value per site in each register), so a site costs 1/S of the
 // instruction dispatch and operands move in S-wide vector accesses.
@@ -844,6 +1381,41 @@ static hipError_t go(int nt, int block, int grid, size_t shm, const ProgArgs &a,
     return hipGetLastError();
 }
 
+template <class T, int S, int FORM>
+static hipError_t go_rows(int nt, size_t shm, const su3i::RowArgs &a, hipStream_t st)
+{
+    const int per = kRowLanes * S;
+    const dim3 grid((unsigned)(((int64_t)a.nsites + per - 1) / per)), block(3 * kRowLanes);
+    const size_t need = (size_t)a.nslots * kRowSlot * S * 2 * sizeof(T);
+    if (shm < need)
+        shm = need;
+    auto *k = (nt & 3) == 3   ? k_program_rows<T, S, 3, FORM>
+              : (nt & 3) == 2 ? k_program_rows<T, S, 2, FORM>
+                              : k_program_rows<T, S, 0, FORM>;
+    if (shm > 64 * 1024) {
+        // beyond the default dynamic LDS of a workgroup (eight slots take
+        // 75 KB)
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)shm);
+        if (e != hipSuccess)
+            return e;
+    }
+    hipLaunchKernelGGL(k, grid, block, shm, st, a);
+    return hipGetLastError();
+}
+
+template <class T, int S>
+static hipError_t pick_rows(int nt, size_t shm, const su3i::RowArgs &a, hipStream_t st)
+{
+    if constexpr (S == 1) {
+        if (a.aos)
+            return a.held ? go_rows<T, 1, ROWF_AOS | ROWF_HELD>(nt, shm, a, st)
+                          : go_rows<T, 1, ROWF_AOS>(nt, shm, a, st);
+    }
+    return a.held ? go_rows<T, S, ROWF_HELD>(nt, shm, a, st) : go_rows<T, S, 0>(nt, shm, a, st);
+}
+
 // Sites per lane of scalar-only programs: 32 bytes of each real operand
 // (two 16-byte accesses).
 template <class T>
@@ -922,6 +1494,22 @@ hipError_t launch_program(int arith, int form, int nregs, int nt,
         return go_t<double>(form, nregs, nt, block, grid, shm, a, st);
     if (arith == F32)
         return go_t<float>(form, nregs, nt, block, grid, shm, a, st);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_program_rows(int arith, int sites_per_lane, int nt, size_t shm,
+                               const RowArgs &a, hipStream_t st)
+{
+    using namespace su3k::prog;
+    if (a.nsites < 1 || a.ninstr < 1 || a.ninstr > kProgMaxInstr || a.nslots < 1 ||
+        a.nslots > kRowMaxSlots)
+        return hipErrorInvalidValue;
+    if (arith == F64 && sites_per_lane == 1)
+        return pick_rows<double, 1>(nt, shm, a, st);
+    if (arith == F32 && sites_per_lane == 1)
+        return pick_rows<float, 1>(nt, shm, a, st);
+    if (arith == F32 && sites_per_lane == 2 && !a.aos)
+        return pick_rows<float, 2>(nt, shm, a, st);
     return hipErrorInvalidValue;
 }
 

@@ -13,6 +13,7 @@
 // combine with matrices as multiples of the identity (s + M adds s to the
 // diagonal, s * M scales), as the lattice expression templates treat a
 // scalar assigned to a matrix-valued field.
+#include <algorithm>
 #include <cctype>
 #include <cstdio>
 #include <cstdlib>
@@ -350,6 +351,259 @@ struct Gen {
     }
 };
 
+// The row form: the same values in the same order of evaluation, but with
+// conjugates, transposes and signs carried as modes of a value and constants
+// as immediates, so that only sums, products, traces, real and imaginary
+// parts are instructions.
+struct RowGen {
+    struct Val {
+        int src;  // virtual register, or ROW_IMM + constant
+        int mode;
+        Ty ty;
+    };
+    struct Ins {
+        int op, a, am, b, bm;  // sources: virtual registers or ROW_IMM + constant
+    };
+    static constexpr int kImm = 1 << 16;
+    std::vector<Ins> ins;  // instruction t defines virtual register nops + t
+    int nops = 0, nimm = 0;
+    bool ok = true;
+
+    Val emit(int op, Val a, Val b, Ty ty)
+    {
+        ins.push_back({op, a.src, a.mode, b.src, b.mode});
+        return {nops + (int)ins.size() - 1, 0, ty};
+    }
+
+    Val gen(const Node *n)
+    {
+        switch (n->kind) {
+        case N_OPERAND: return {n->operand, 0, n->ty};
+        case N_CONST: return {kImm + nimm++, 0, n->ty};
+        case N_NEG: {
+            Val a = gen(n->l.get());
+            a.mode ^= ROW_NEG;
+            return a;
+        }
+        case N_FUNC: {
+            Val a = gen(n->l.get());
+            switch (n->func) {
+            case F_ADJ:
+                if (a.ty == T_MATRIX)
+                    a.mode ^= ROW_CONJ | ROW_TRANS;
+                else if (a.ty == T_COMPLEX)
+                    a.mode ^= ROW_CONJ;
+                return a;
+            case F_CONJ:
+                if (a.ty != T_REAL)
+                    a.mode ^= ROW_CONJ;
+                return a;
+            case F_TRANS:
+                if (a.ty == T_MATRIX)
+                    a.mode ^= ROW_TRANS;
+                return a;
+            case F_TRACE: {
+                if (a.ty != T_MATRIX)
+                    return a;
+                // the trace of a conjugate or negative is the trace's
+                const int mode = a.mode & (ROW_CONJ | ROW_NEG);
+                a.mode = 0;
+                Val t = emit(ROW_TRACE, a, a, T_COMPLEX);
+                t.mode = mode;
+                return t;
+            }
+            case F_REAL:
+                return a.ty == T_COMPLEX ? emit(ROW_REAL, a, a, T_REAL) : a;
+            case F_IMAG: return emit(ROW_IMAG, a, a, T_REAL);
+            }
+            return a;
+        }
+        default: {
+            Val a, b;
+            if (n->r->need > n->l->need) {  // the order of the register form
+                b = gen(n->r.get());
+                a = gen(n->l.get());
+            } else {
+                a = gen(n->l.get());
+                b = gen(n->r.get());
+            }
+            const bool ma = a.ty == T_MATRIX, mb = b.ty == T_MATRIX;
+            if (n->kind == N_MUL) {
+                if (ma && mb) {
+                    a.mode ^= b.mode & ROW_NEG;  // the sign on the left factor
+                    b.mode &= ~ROW_NEG;
+                    return emit(ROW_MUL_M, a, b, T_MATRIX);
+                }
+                if (ma || mb)
+                    return emit(ma ? ROW_MUL_MS : ROW_MUL_SM, a, b, T_MATRIX);
+                return emit(ROW_MUL_S, a, b, n->ty);
+            }
+            if (n->kind == N_SUB)
+                b.mode ^= ROW_NEG;  // x - y = x + (-y), bit for bit
+            if (ma && mb)
+                return emit(ROW_ADD_M, a, b, T_MATRIX);
+            if (ma)
+                return emit(ROW_ADD_MS, a, b, T_MATRIX);
+            if (mb)
+                return emit(ROW_ADD_MS, b, a, T_MATRIX);
+            return emit(ROW_ADD_S, a, b, n->ty);
+        }
+        }
+    }
+
+    static bool binary(int op)
+    {
+        return op == ROW_ADD_M || op == ROW_MUL_M || op == ROW_MUL_SM || op == ROW_MUL_MS ||
+               op == ROW_ADD_MS || op == ROW_ADD_S || op == ROW_MUL_S;
+    }
+    static bool matrix_a(int op)
+    {
+        return op == ROW_MOV_M || op == ROW_ADD_M || op == ROW_MUL_M || op == ROW_MUL_MS ||
+               op == ROW_ADD_MS || op == ROW_TRACE;
+    }
+    static bool matrix_b(int op)
+    {
+        return op == ROW_ADD_M || op == ROW_MUL_M || op == ROW_MUL_SM;
+    }
+    // Reads of rows that other waves hold: a product's right operand, a
+    // trace, and any transposed matrix.
+    static bool crosses(const Ins &i, bool b)
+    {
+        if (b)
+            return i.op == ROW_MUL_M || (matrix_b(i.op) && (i.bm & ROW_TRANS));
+        return i.op == ROW_TRACE || (matrix_a(i.op) && (i.am & ROW_TRANS));
+    }
+
+    enum Registers { NO_REGISTERS, HOLD_RESULTS, HOLD_ALL };
+
+    // Slots, registers and barriers; false when it does not fit.
+    bool lower(Val res, unsigned used, Registers regs, RowCode *out)
+    {
+        if (res.src != nops + (int)ins.size() - 1 || res.mode != 0 || ins.empty())
+            ins.push_back({res.ty == T_MATRIX ? ROW_MOV_M : ROW_MOV_S, res.src, res.mode, res.src,
+                           res.mode});
+        const int n = (int)ins.size(), nv = nops + n;
+        if (n > kProgMaxInstr)
+            return false;
+        for (int t = 0; t < n; ++t) {
+            // the last result as the left term of a (commutative) sum
+            Ins &i = ins[t];
+            if ((i.op == ROW_ADD_M || i.op == ROW_ADD_S) && i.b == nops + t - 1 &&
+                !crosses(i, true)) {
+                std::swap(i.a, i.b);
+                std::swap(i.am, i.bm);
+            }
+        }
+        // a value read by the next instruction only, from its own rows, stays
+        // in the accumulator
+        std::vector<int> last(nv, -1);
+        const auto from_acc = [&](int t, bool b) {
+            const Ins &i = ins[t];
+            return (b ? i.b : i.a) == nops + t - 1 && t > 0 && !crosses(i, b);
+        };
+        for (int t = 0; t < n; ++t)
+            for (int b = 0; b < (binary(ins[t].op) ? 2 : 1); ++b) {
+                const int v = b ? ins[t].b : ins[t].a;
+                if (v < kImm && !from_acc(t, b))
+                    last[v] = t;
+            }
+        // registers hold values that no other wave reads
+        std::vector<char> shared(nv, 0);
+        for (int t = 0; t < n; ++t)
+            for (int b = 0; b < (binary(ins[t].op) ? 2 : 1); ++b)
+                if ((b ? ins[t].b : ins[t].a) < kImm && crosses(ins[t], b))
+                    shared[b ? ins[t].b : ins[t].a] = 1;
+        int held[kRowRegisters];
+        std::fill(held, held + kRowRegisters, -1);
+        const auto hold = [&](int v) {
+            for (int k = 0; k < kRowRegisters; ++k)
+                if (regs != NO_REGISTERS && !shared[v] && held[k] < 0) {
+                    held[k] = v;
+                    return ROW_ACC + 1 + k;
+                }
+            return -1;
+        };
+        std::vector<int> slot(nv, -1), owner, written, crossed;
+        const auto take = [&](int v) {
+            for (size_t k = 0; k < owner.size(); ++k)
+                if (owner[k] < 0) {
+                    owner[k] = v;
+                    return (int)k;
+                }
+            owner.push_back(v);
+            written.push_back(0);
+            crossed.push_back(-1);
+            return (int)owner.size() - 1;
+        };
+        for (int k = 0; k < nops; ++k)
+            if (used >> k & 1) {
+                slot[k] = regs == HOLD_ALL ? hold(k) : -1;
+                if (slot[k] < 0)
+                    slot[k] = take(k);
+                out->slot[k] = (uint8_t)slot[k];
+            }
+        int epoch = 0;
+        for (int t = 0; t < n; ++t) {
+            const Ins &i = ins[t];
+            RowInstr &r = out->ins[t];
+            r = RowInstr{(uint8_t)i.op, ROW_NONE, 0, (uint8_t)i.am, 0, (uint8_t)i.bm, 0, 0};
+            const int nsrc = binary(i.op) ? 2 : 1;
+            for (int b = 0; b < nsrc; ++b) {
+                const int v = b ? i.b : i.a;
+                const int src = v >= kImm        ? ROW_IMM + (v - kImm)
+                                : from_acc(t, b) ? ROW_ACC
+                                                 : slot[v];
+                if (src < 0)
+                    return false;
+                (b ? r.b : r.a) = (uint8_t)src;
+                if (crosses(i, b) && src < ROW_IMM && written[src] == epoch)
+                    r.flags |= ROW_SYNC_READ;
+            }
+            if (r.flags & ROW_SYNC_READ)
+                ++epoch;
+            for (int b = 0; b < nsrc; ++b) {
+                const int src = b ? r.b : r.a;
+                if (crosses(i, b) && src < ROW_IMM)
+                    crossed[src] = epoch;
+            }
+            for (size_t k = 0; k < owner.size(); ++k)
+                if (owner[k] >= 0 && last[owner[k]] <= t)
+                    owner[k] = -1;
+            for (int &v : held)
+                if (v >= 0 && last[v] <= t)
+                    v = -1;
+            if (last[nops + t] < 0)
+                continue;  // read from the accumulator only, or the result
+            slot[nops + t] = hold(nops + t);
+            if (slot[nops + t] >= 0) {
+                r.d = (uint8_t)slot[nops + t];
+                continue;
+            }
+            // a free slot that no wave may still be reading, if there is one
+            int d = -1;
+            for (size_t k = 0; k < owner.size() && d < 0; ++k)
+                if (owner[k] < 0 && crossed[k] != epoch)
+                    d = (int)k;
+            if (d < 0)
+                d = take(nops + t);
+            owner[d] = nops + t;
+            slot[nops + t] = d;
+            r.d = (uint8_t)d;
+            if (crossed[d] == epoch) {
+                r.flags |= ROW_SYNC_WRITE;
+                ++epoch;
+            }
+            written[d] = epoch;
+        }
+        if ((int)owner.size() > kRowMaxSlots)
+            return false;
+        out->n = n;
+        out->held = regs != NO_REGISTERS;
+        out->nslots = owner.empty() ? 1 : (int)owner.size();
+        return true;
+    }
+};
+
 }  // namespace
 
 bool compile_program(const char *text, int nops, const int *kinds,
@@ -466,6 +720,24 @@ bool compile_program(const char *text, int nops, const int *kinds,
     for (int k = 0; k < nops; ++k)
         if (last[k] >= 0)
             out->used |= 1u << k;
+    if (!out->scalar_only) {
+        RowGen rg;
+        rg.nops = nops;
+        const RowGen::Val v = rg.gen(root.get());
+        // (an operand that is the whole expression is read too)
+        unsigned used = 0;
+        for (const RowGen::Ins &i : rg.ins)
+            for (int src : {i.a, i.b})
+                if (src < nops)
+                    used |= 1u << src;
+        if (v.src < nops)
+            used |= 1u << v.src;
+        RowGen held = rg, aos = rg;
+        if (used != out->used || !rg.lower(v, used, RowGen::NO_REGISTERS, &out->rows) ||
+            !held.lower(v, used, RowGen::HOLD_ALL, &out->rows_held) ||
+            !aos.lower(v, used, RowGen::HOLD_RESULTS, &out->rows_aos))
+            out->rows.n = 0;
+    }
     return true;
 }
 
