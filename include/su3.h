@@ -417,16 +417,17 @@ su3_status su3_program_info(const su3_program *p, su3_kind *result_kind,
  * field is SU3_F32 or SU3_C12_F32 (mixed: SU3_ERR_MISMATCH; half:
  * SU3_ERR_UNSUPPORTED).  A compressed output needs an SU(3)-valued
  * expression (products, adj, transpose, conj of matrices)
- * (SU3_ERR_UNSUPPORTED otherwise).  Programs with matrix values run in
- * kernel variants of 2, 4 or 8 registers; the 8-register one runs one
- * wave per SIMD in double and two in single, and is slower per byte than
- * the others.  z may be an operand exactly; a partial overlap is
- * SU3_ERR_ALIAS.  The launch setting of SU3_EXPR_PROGRAM (tuned or set)
- * applies in full to programs with matrix values and a matrix result,
- * that of SU3_EXPR_PROGRAM_SCALAR to programs with matrix values and a
- * real or complex result; programs without a matrix value
- * take only its nontemporal bits and run 256-lane workgroups with no
- * occupancy cap. */
+ * (SU3_ERR_UNSUPPORTED otherwise).  Programs with matrix values run with one
+ * wave per matrix row and their values in LDS, or one site per lane in
+ * variants of 2, 4 or 8 registers, whichever is faster for the lattice,
+ * layout and expression (the same bits).  z may be an operand exactly; a
+ * partial overlap is SU3_ERR_ALIAS.  The launch setting of SU3_EXPR_PROGRAM
+ * (tuned or set) applies to programs with matrix values and a matrix result
+ * (workgroups of three waves ignore its block), that of
+ * SU3_EXPR_PROGRAM_SCALAR to programs with matrix values and a real or complex
+ * result; a call without one takes cached or streaming loads and its occupancy
+ * cap by its bytes and layout.  Programs without a matrix value take only its
+ * nontemporal bits and run 256-lane workgroups with no occupancy cap. */
 su3_status su3_program_eval(const su3_program *p, su3_field *z,
                             const su3_field *const *ops, int32_t n_ops,
                             void *stream);

@@ -1845,25 +1845,27 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
     return &pc.rows;
 }
 
-// The launch of a matrix program that nothing tuned or set (rows: its row
-// form).  Loads stay cached in calls that the Infinity Cache holds with the
-// fields in use around them (FP32 24^4 a*adj(b), 72 MB: 12.9 us against 14.3),
+// The launch of a program that nothing tuned or set (rows: its row form).
+// Loads stay cached in calls that the Infinity Cache holds with the fields in
+// use around them (FP32 24^4 a*adj(b), 72 MB: 12.9 us against 14.3; FP64
+// 48^3 x 24 a+b+a*b on real fields, 64 MB: 11.9 against 12.6),
 // where a lane-block's entry is less than a 128-byte line (FP32 AoSoA-8 32^4
 // a*b+c*d: 66.6 us against 72.9), and for AoS sites read entry by entry.  One
 // product alone streams best with 5 workgroups per CU (FP64 48^4 a*adj(b):
 // 361 us, uncapped 405); longer programs want them all.
 static su3_launch program_launch(const su3_program *p, const su3_field *z,
                                  const su3_field *const *ops, int arith, const RowCode *rows,
-                                 su3_expr key)
+                                 int form)
 {
-    su3_launch c = default_launch(key, arith, z->layout, z->V);
+    su3_launch c = default_launch(SU3_EXPR_PROGRAM, arith, z->layout, z->V);
     int64_t bytes = (int64_t)z->bytes;
     for (int k = 0; k < p->code.nops; ++k)
         if (p->code.used >> k & 1)
             bytes += (int64_t)ops[k]->bytes;
     const int64_t MB = 1000 * 1000;
     const bool aos = z->layout == SU3_LAYOUT_AOS;
-    const bool split = aos ? !rows : z->L * 2 * (int64_t)real_bytes(arith) < 128;
+    const bool split = form == PF_MATRIX &&
+                       (aos ? !rows : z->L * 2 * (int64_t)real_bytes(arith) < 128);
     c.nontemporal = bytes <= 150 * MB || split ? 2 : 3;
     if (rows && rows->n == 1 && bytes > 256 * MB && !aos)
         c.occupancy = 5;
@@ -1888,8 +1890,7 @@ static su3_status launch_program_op(const su3_program *p, su3_field *z,
     if (forced)
         c = *forced;
     else if (!tuned_launch(key, arith, z->layout, z->lanes, z->V, &c))
-        c = form == PF_MATRIX ? program_launch(p, z, ops, arith, rows, key)
-                              : default_launch(key, arith, z->layout, z->V);
+        c = program_launch(p, z, ops, arith, rows, form);
     if (!forced && form != PF_MATRIX) {
         // the block and occupancy cap are the matrix kernel's (a wave of it
         // keeps up to 18 KB of loads in flight); a scalar-valued wave keeps

@@ -1,5 +1,7 @@
-// Program kernel: evaluates a compiled site-local expression (see
-// su3_program.cpp) at every site.  One site per lane.  The operand fields
+// Program kernels: evaluate a compiled site-local expression (see
+// su3_program.cpp) at every site.  Most programs with matrix values run in
+// the row form (k_program_rows, below); k_program takes the rest, one site
+// per lane.  The operand fields
 // the program reads are loaded into registers 0 .. nops-1 up front, so all
 // of a lane's loads are in flight together; the instructions then run on
 // registers, each a uniform branch on the opcode (matrix programs through
@@ -458,9 +460,16 @@ __global__ __launch_bounds__(256) void k_program(ProgArgs a)
 // entry and lane), wave r the row r.  Values live in LDS slots of 9 entries,
 // so an instruction's operand is an address -- no selection of registers by
 // chains of branches and copies, which cost the one-lane interpreter more
-// than its arithmetic -- and a lane needs registers for a few rows only: the
-// waves a CU holds are set by the slots a program needs (9.1 KiB each), 24
-// for two slots, 6 for seven, against 4 in double for the one-lane kernel.
+// than its arithmetic (force term FP64 32^4: 1130 VALU instructions a wave,
+// some 250 of them arithmetic) -- and a lane needs registers for a few rows
+// only: the waves a CU holds are set by the slots a program needs (9.1 KiB
+// each), 24 for two slots, 12 for four, against 4 in double for the one-lane
+// kernel.  What bounds it is the latency of LDS and memory those waves hide:
+// a six-slot program holds the values no other wave reads in registers and
+// so fits four slots.  Measured, one-lane kernel and here:
+// (a*b+c*d)*(a*c+b*d)+(a-b)*(c-d) FP64 32^4 303 -> 222 us (755 MB), 8^4 18.6
+// -> 9.1, FP32 48^4 560 -> 517; a*b-adj(b)*adj(a) FP64 48^4 494 -> 369 (6.2
+// TB/s), FP32 16^4 7.1 -> 5.7; trace(a*b*adj(c)*adj(d)) FP64 48^4 660 -> 553.
 // The last result is also in the accumulator Z.  A product reads its right
 // operand's rows, a transposed operand its columns and a trace its diagonal
 // from the slots the other waves wrote; the host sets the barriers that need
@@ -988,52 +997,112 @@ __global__ __launch_bounds__(3 * kRowLanes) void k_program_rows(su3i::RowArgs a)
     }
 }
 
-// Scalar-only programs: each lane evaluates S consecutive sites (one
-// complex value per site in each register), so a site costs 1/S of the
-// instruction dispatch and operands move in S-wide vector accesses.
+// Scalar-only programs: each lane evaluates S sites (one complex value per
+// site in each register), so a site costs 1/S of the instruction dispatch.
+// A lane's sites are S / W vectors of W, W the sites of 16 bytes of a complex
+// field (1 in double, 2 in single): vector q of lane l in the lane group
+// g = gid / 64 is vector (S / W g + q) * 64 + l of the field, so each access
+// of a wave is 1 KiB of consecutive bytes (512 of a real field).  Bound by
+// memory: with 4 (double) or 8 (single) sites side by side in a lane, 16
+// bytes 64 apart, nontemporal loads fetched every line four times (a*conj(b)+a
+// FP32 48^4, 127 MB: 172 us, now 26.6; FP64, 255 MB: 161, now 46), and the
+// smallest lattices waited for eight sites' copies (FP32 8^4 8.9, now 5.2).
+template <class T>
+constexpr int kScalarVec = 8 / sizeof(T);
+
 template <class T, int S>
 struct SReg {
     Cx<T> v[S];
 };
 
+// Vectors v0 + 64 q; vectors past the end read as 0.
 template <class T, int S, int NT>
-__device__ __forceinline__ void load_scalars(const ProgArgs &a, int k, uint32_t s0,
-                                             int cnt, SReg<T, S> &r)
+__device__ __forceinline__ void load_scalars(const ProgArgs &a, int k, uint32_t v0, uint32_t n,
+                                             SReg<T, S> &r)
 {
-    if (a.kind[k] == su3i::FK_REAL) {
-        const T *p = static_cast<const T *>(a.op[k]) + s0;
-        if (cnt == S) {
-            // 16-byte pieces
-            constexpr int W = 16 / sizeof(T);
-            using V = typename VecOf<T, W>::type;
+    constexpr int W = kScalarVec<T>;
+    const bool real = a.kind[k] == su3i::FK_REAL;
 #pragma unroll
-            for (int q = 0; q < S / W; ++q) {
-                const V w = vload<NT & 1>(reinterpret_cast<const V *>(p) + q);
+    for (int q = 0; q < S / W; ++q) {
+        const uint32_t s0 = (v0 + 64u * q) * W;
+        if (s0 + W <= n) {
+            if (real) {
+                const T *p = static_cast<const T *>(a.op[k]) + s0;
+                if constexpr (W == 1) {
+                    r.v[q] = {vload<NT & 1>(p), T(0)};
+                } else {
+                    using V = typename VecOf<T, W>::type;
+                    const V w = vload<NT & 1>(reinterpret_cast<const V *>(p));
+#pragma unroll
+                    for (int j = 0; j < W; ++j)
+                        r.v[q * W + j] = {w[j], T(0)};
+                }
+                branch_end<40>();
+            } else {
+                using V = typename VecOf<T, 2 * W>::type;
+                const V w = vload<NT & 1>(
+                    reinterpret_cast<const V *>(static_cast<const T *>(a.op[k]) + 2 * s0));
 #pragma unroll
                 for (int j = 0; j < W; ++j)
-                    r.v[q * W + j] = {w[j], T(0)};
+                    r.v[q * W + j] = {w[2 * j], w[2 * j + 1]};
+                branch_end<41>();
             }
         } else {
+            const T *p = static_cast<const T *>(a.op[k]);
 #pragma unroll
-            for (int j = 0; j < S; ++j)
-                r.v[j] = {j < cnt ? p[j] : T(0), T(0)};
-        }
-        branch_end<40>();
-    } else {
-        using V2 = typename VecOf<T, 2>::type;
-        const V2 *p = static_cast<const V2 *>(a.op[k]) + s0;
-#pragma unroll
-        for (int j = 0; j < S; ++j) {
-            V2 w;
-            if (cnt == S || j < cnt) {
-                w = vload<NT & 1>(p + j);
-            } else {
-                w[0] = T(0);
-                w[1] = T(0);
+            for (int j = 0; j < W; ++j) {
+                r.v[q * W + j] = {T(0), T(0)};
+                if (s0 + j < n) {
+                    if (real)
+                        r.v[q * W + j].re = p[s0 + j];
+                    else
+                        r.v[q * W + j] = {p[2 * (s0 + j)], p[2 * (s0 + j) + 1]};
+                }
             }
-            r.v[j] = {w[0], w[1]};
         }
-        branch_end<41>();
+    }
+}
+
+template <class T, int S, int NT>
+__device__ __forceinline__ void store_scalars(const ProgArgs &a, uint32_t v0, uint32_t n,
+                                              const SReg<T, S> &Z)
+{
+    constexpr int W = kScalarVec<T>;
+    T *z = static_cast<T *>(a.z);
+#pragma unroll
+    for (int q = 0; q < S / W; ++q) {
+        const uint32_t s0 = (v0 + 64u * q) * W;
+        if (a.zkind == su3i::FK_REAL) {
+            if (W > 1 && s0 + W <= n) {
+                using V = typename VecOf<T, W>::type;
+                V w;
+#pragma unroll
+                for (int j = 0; j < W; ++j)
+                    w[j] = Z.v[q * W + j].re;
+                vstore<NT & 2>(reinterpret_cast<V *>(z + s0), w);
+            } else {
+#pragma unroll
+                for (int j = 0; j < W; ++j)
+                    if (s0 + j < n)
+                        vstore<NT & 2>(z + s0 + j, Z.v[q * W + j].re);
+            }
+        } else if (s0 + W <= n) {
+            using V = typename VecOf<T, 2 * W>::type;
+            V w;
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                w[2 * j] = Z.v[q * W + j].re;
+                w[2 * j + 1] = Z.v[q * W + j].im;
+            }
+            vstore<NT & 2>(reinterpret_cast<V *>(z + 2 * s0), w);
+        } else {
+#pragma unroll
+            for (int j = 0; j < W; ++j)
+                if (s0 + j < n) {
+                    z[2 * (s0 + j)] = Z.v[q * W + j].re;
+                    z[2 * (s0 + j) + 1] = Z.v[q * W + j].im;
+                }
+        }
     }
 }
 
@@ -1085,17 +1154,17 @@ __device__ __forceinline__ void sput(RegFile<T, S, NR> &R, int i, const SReg<T, 
 }
 
 template <class T, int S, int NR, int NT, int K = 0>
-__device__ __forceinline__ void sload_all(const ProgArgs &a, uint32_t s0, int cnt,
+__device__ __forceinline__ void sload_all(const ProgArgs &a, uint32_t v0, uint32_t n,
                                           RegFile<T, S, NR> &R)
 {
     if constexpr (K < NR) {
         if (K < a.nops) {
             if ((a.used >> K) & 1) {
                 SReg<T, S> t;
-                load_scalars<T, S, NT>(a, K, s0, cnt, t);
+                load_scalars<T, S, NT>(a, K, v0, n, t);
                 sput<T, S, NR>(R, K, t);
             }
-            sload_all<T, S, NR, NT, K + 1>(a, s0, cnt, R);
+            sload_all<T, S, NR, NT, K + 1>(a, v0, n, R);
         }
     }
 }
@@ -1105,11 +1174,13 @@ template <class T, int S, int NR, int NT>
 __global__ __launch_bounds__(256) void k_program_scalar(ProgArgs a)
 {
     extern __shared__ char occupancy_reserve[];
-    const uint32_t s0 = (blockIdx.x * blockDim.x + threadIdx.x) * S;
-    if (s0 < (uint32_t)a.nsites) {
-        const int cnt = (uint32_t)a.nsites - s0 < (uint32_t)S ? int(a.nsites - s0) : S;
+    constexpr int W = kScalarVec<T>;
+    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t v0 = (gid >> 6) * (64u * (S / W)) + (gid & 63u);
+    const uint32_t n = (uint32_t)a.nsites;
+    if (a.nsites > 0 && v0 * W < n) {
         RegFile<T, S, NR> R;
-        sload_all<T, S, NR, NT>(a, s0, cnt, R);
+        sload_all<T, S, NR, NT>(a, v0, n, R);
         for (int pc = 0; pc < a.ninstr; ++pc) {
             const ProgInstr in = a.ins[pc];
             SReg<T, S> A, B, C;
@@ -1120,37 +1191,7 @@ __global__ __launch_bounds__(256) void k_program_scalar(ProgArgs a)
         }
         SReg<T, S> Z;
         sget(R, a.result, Z);
-        if (a.zkind == su3i::FK_REAL) {
-            T *p = static_cast<T *>(a.z) + s0;
-            if (cnt == S) {
-                constexpr int W = 16 / sizeof(T);
-                using V = typename VecOf<T, W>::type;
-#pragma unroll
-                for (int q = 0; q < S / W; ++q) {
-                    V w;
-#pragma unroll
-                    for (int j = 0; j < W; ++j)
-                        w[j] = Z.v[q * W + j].re;
-                    vstore<NT & 2>(reinterpret_cast<V *>(p) + q, w);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < S; ++j)
-                    if (j < cnt)
-                        p[j] = Z.v[j].re;
-            }
-        } else {
-            using V2 = typename VecOf<T, 2>::type;
-            V2 *p = static_cast<V2 *>(a.z) + s0;
-#pragma unroll
-            for (int j = 0; j < S; ++j)
-                if (cnt == S || j < cnt) {
-                    V2 w;
-                    w[0] = Z.v[j].re;
-                    w[1] = Z.v[j].im;
-                    vstore<NT & 2>(p + j, w);
-                }
-        }
+        store_scalars<T, S, NT>(a, v0, n, Z);
     }
     if (a.nsites < 0)
         occupancy_reserve[threadIdx.x] = 0;
@@ -1416,10 +1457,12 @@ static hipError_t pick_rows(int nt, size_t shm, const su3i::RowArgs &a, hipStrea
     return a.held ? go_rows<T, S, ROWF_HELD>(nt, shm, a, st) : go_rows<T, S, 0>(nt, shm, a, st);
 }
 
-// Sites per lane of scalar-only programs: 32 bytes of each real operand
-// (two 16-byte accesses).
+// Sites per lane of real-valued programs: 32 bytes of each operand (two
+// 16-byte accesses); of scalar-only ones 32 bytes of each complex operand.
 template <class T>
-constexpr int kScalarSites = 32 / sizeof(T);
+constexpr int kRealSites = 32 / sizeof(T);
+template <class T>
+constexpr int kScalarSites = 16 / sizeof(T);
 
 template <class T, int NR>
 static hipError_t go_scalar(int nt, int block, int grid, size_t shm,
@@ -1439,7 +1482,7 @@ template <class T, int NR>
 static hipError_t go_real(int nt, int block, int grid, size_t shm,
                           const ProgArgs &a, hipStream_t st)
 {
-    constexpr int S = kScalarSites<T>;
+    constexpr int S = kRealSites<T>;
     if ((nt & 3) == 3)
         hipLaunchKernelGGL((k_program_real<T, S, NR, 3>), dim3(grid), dim3(block), shm, st, a);
     else if ((nt & 3) == 2)
@@ -1478,6 +1521,8 @@ int program_sites_per_lane(int arith, int form)
 {
     if (form == PF_MATRIX)
         return 1;
+    if (form == PF_REAL)
+        return arith == F64 ? su3k::prog::kRealSites<double> : su3k::prog::kRealSites<float>;
     return arith == F64 ? su3k::prog::kScalarSites<double>
                         : su3k::prog::kScalarSites<float>;
 }
