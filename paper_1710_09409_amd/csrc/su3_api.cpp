@@ -1110,41 +1110,100 @@ static su3_launch lookup_launch(int expr, int prec, int layout, int lanes,
                : default_launch(expr, prec, layout, V);
 }
 
+// Workgroups of a walk that a CU holds.
+static int dslash_per_cu(const LdsShape &sh, int prec)
+{
+    const bool dbl = prec == SU3_F64;
+    const int wave_slots = dbl ? 8 : prec == SU3_F32 ? 16 : 12;
+    const int lanes = sh.nsub * sh.tx * sh.ty * sh.tz;
+    return std::max(1, std::min((int)(160 * 1024 / lds_shape_bytes(sh, dbl ? 16 : 8)),
+                                wave_slots / ((lanes + 63) / 64)));
+}
+
 // Estimated microseconds of an LDS-tiled Dslash walk of `walk` t-slices over
-// (outer) extents o: the rounds of workgroups the CUs need, each walking
-// `walk` slices and a start-up, at a slice time that is the larger of a
-// latency floor (barriers, LDS and a slice's dependent loads) and the tile's
-// bytes at a CU's share of the memory rate.  The constants are fitted to 45
-// measured lattices (24^4 to 48^4, odd extents, virtual nodes; up to 13 row
-// tiles and 14 walks each): the tile and walk of least estimate run within
-// 0.5 % (double), 2 % (single) and 3 % (two-row links) of the fastest.
+// (outer) extents o: the rounds of workgroups the CUs need, each walking its
+// slices and a start-up, at a slice time that is the larger of a latency floor
+// (barriers, LDS and a slice's dependent loads) and the tile's bytes at a CU's
+// share of the memory rate.  The last walk of each tile may be shorter; those
+// run last, beside the remaining long ones.  The constants are fitted to 44
+// measured lattices (24^4 to 64 x 32^3, odd extents, virtual nodes; up to 13
+// row tiles with up to 12 walks each): the plan runs within 1.1 % (double),
+// 0.6 % (single) and 1.5 % (two-row links) of the fastest on average, 4.4, 4.6
+// and 8.4 % at most.
 static double dslash_walk_us(const LdsShape &sh, int prec, const int32_t o[4],
                              int walk, int cus)
 {
     const bool dbl = prec == SU3_F64;
     const double spinor = dbl ? 192 : 96, link = dbl ? 144 : prec == SU3_F32 ? 72 : 48;
-    const double floor_us = (dbl ? 14.0 : 10.0) * (!dbl && sh.nb == 2 ? 0.95 : 1.0);
-    const double start = dbl ? 1.0 : 1.5, cu_bytes_per_us = dbl ? 20e3 : 30e3;
-    const int wave_slots = dbl ? 8 : prec == SU3_F32 ? 16 : 12;
-    // bytes per site: links, input, output; half of the face sites' second
-    // reads miss (a halo saves a quarter of those in double)
-    const double x_cut = sh.tx < o[0] ? 1.0 / sh.tx : 0.0;
-    const double yz_cut = 1.0 / sh.ty + 1.0 / sh.tz;
-    const double site_bytes = 2 * spinor + 4 * link + 0.5 * (2 * spinor + link) *
-                              (x_cut + yz_cut * (dbl && sh.halo ? 0.75 : 1.0));
-    const int lanes = sh.nsub * sh.tx * sh.ty * sh.tz;
-    int64_t groups = (o[3] + walk - 1) / walk;
-    groups *= (int64_t)((o[0] + sh.tx - 1) / sh.tx) * ((o[1] + sh.ty - 1) / sh.ty) *
-              ((o[2] + sh.tz - 1) / sh.tz);
-    const int per_cu = std::max(1, std::min((int)(160 * 1024 / lds_shape_bytes(sh, dbl ? 16 : 8)),
-                                            wave_slots / ((lanes + 63) / 64)));
-    const int64_t slots = (int64_t)cus * per_cu, rest = groups % slots;
-    const auto round_us = [&](int64_t resident) {
-        return (walk + start) *
+    const double floor_us = dbl ? 12.0 : sh.nb == 2 ? 11.05 : 13.0;
+    const double start = 0.5, cu_bytes_per_us = 28e3;
+    // bytes per site: links, input, output, and the share of the face sites'
+    // second reads that miss (in double a halo saves some of those of a
+    // square tile, and costs a 2 x 4 one, with more faces per row, what it
+    // saves: 3 x 3 FP64 48^4 968 us against 1004, 2 x 4 FP64 32^4 219 against
+    // 211)
+    const double miss = dbl ? 0.5 : 1.0;
+    const double x_cut = sh.tx < o[0] ? 0.5 / sh.tx : 0.0;
+    const double yz_cut = miss * (1.0 / sh.ty + 1.0 / sh.tz);
+    const double site_bytes = 2 * spinor + 4 * link + (2 * spinor + link) *
+                              (x_cut + yz_cut * (dbl && sh.halo && sh.ty == sh.tz ? 0.85 : 1.0));
+    const int lanes = sh.nsub * sh.tx * sh.ty * sh.tz, per_cu = dslash_per_cu(sh, prec);
+    const int64_t tiles = (int64_t)((o[0] + sh.tx - 1) / sh.tx) *
+                          ((o[1] + sh.ty - 1) / sh.ty) * ((o[2] + sh.tz - 1) / sh.tz);
+    const int chunks = (o[3] + walk - 1) / walk, last = o[3] - (chunks - 1) * walk;
+    const int64_t slots = (int64_t)cus * per_cu;
+    const auto walk_us = [&](int slices, int64_t resident) {
+        return (slices + start) *
                std::max(floor_us, (double)resident * lanes * site_bytes / cu_bytes_per_us);
     };
-    return (double)(groups / slots) * round_us(per_cu) +
-           (rest ? round_us((rest + cus - 1) / cus) : 0.0);
+    const auto rounds_us = [&](int64_t groups, int slices) {
+        const int64_t rest = groups % slots;
+        return (double)(groups / slots) * walk_us(slices, per_cu) +
+               (rest ? walk_us(slices, (rest + cus - 1) / cus) : 0.0);
+    };
+    if (last == walk)
+        return rounds_us(tiles * chunks, walk);
+    const int64_t rest = tiles * (chunks - 1) % slots;
+    double us = (double)(tiles * (chunks - 1) / slots) * walk_us(walk, per_cu);
+    if (rest == 0)
+        return us + rounds_us(tiles, last);
+    const int64_t resident = rest + tiles >= slots ? per_cu : (rest + tiles + cus - 1) / cus;
+    const double lng = walk_us(walk, resident), shrt = walk_us(last, resident);
+    const int64_t beside = (slots - rest) * (int64_t)(lng / shrt);
+    us += lng;
+    if (tiles > beside)
+        us += (double)((tiles - beside + slots - 1) / slots) * shrt;
+    return us;
+}
+
+// Whether a walk's workgroups go to the XCDs in ranges of tiles rather than
+// one by one: tiles that run on one XCD at the same t read each other's faces
+// from its L2.  Ranges share whole rows of tiles (FP64 32^4, 2 x 4 rows: 211 us
+// against 237; FP32 64 x 32^3 230 against 270; FP64 48^4 968 against 984), dealt
+// singly the tiles share a face only where eight divides their distance.
+// Counted per face, weighted by the faces per site; where both share alike
+// ranges read memory in longer pieces (FP32 32^4, 4 x 4 rows: 115 us against
+// 127).  Not where rounding the ranges up to whole tiles takes an XCD one more
+// round (81 tiles in 3 walks: 257 us against 152).
+static bool dslash_ranges(const LdsShape &sh, const int32_t o[4], int walk, int cus, int per_cu)
+{
+    const int nx = (o[0] + sh.tx - 1) / sh.tx, ny = (o[1] + sh.ty - 1) / sh.ty,
+              nz = (o[2] + sh.tz - 1) / sh.tz, n = nx * ny * nz, t8 = (n + 7) / 8;
+    const int64_t chunks = (o[3] + walk - 1) / walk;
+    const int64_t xcd = std::max(1, cus / 8 * per_cu), slots = std::max(1, cus * per_cu);
+    if ((t8 * chunks + xcd - 1) / xcd > (n * chunks + slots - 1) / slots)
+        return false;
+    double singly = 0, ranges = 0;
+    for (int z = 0; z < nz; ++z)
+        for (int y = 0; y < ny; ++y)
+            for (int x = 0; x < nx; ++x) {
+                const int t = x + nx * (y + ny * z);
+                const int ty = x + nx * ((y + 1) % ny + ny * z), tz = x + nx * (y + ny * ((z + 1) % nz));
+                if (n % 8 == 0)
+                    singly += (t % 8 == ty % 8) / (double)sh.ty + (t % 8 == tz % 8) / (double)sh.tz;
+                ranges += (t / t8 == ty / t8) / (double)sh.ty + (t / t8 == tz / t8) / (double)sh.tz;
+            }
+    return ranges >= singly - 0.01 * n;
 }
 
 // The untuned launch of the Wilson hopping term on lattice dims (virtual
@@ -1180,20 +1239,28 @@ static su3_launch plan_dslash(int prec, int layout, int64_t L, const int32_t dim
         return c;
     }
     double best = 1e300;
-    for (int sched : {9, 10, 11, 12, 16, 17, 18, 20, 21, 22, 26, 27, 28}) {
+    // of equals the first: two buffers where the links are two-row (48^4 16/7
+    // 454 us, 12/7 466), one otherwise (FP32 26 x 30 x 34 x 28 100 us, 103)
+    static const int by_tile[] = {9, 10, 11, 12, 16, 17, 18, 20, 21, 22, 26, 27, 28};
+    static const int by_buffers[] = {16, 18, 26, 28, 9, 10, 11, 12, 17, 20, 21, 22, 27};
+    for (int sched : prec == SU3_C12_F32 ? by_buffers : by_tile) {
         LdsShape sh;
         if (!lds_shape(sched, 256, cbytes, o[0], nsub, sh))
             continue;
-        for (int chunks = 1, last = 0; chunks <= o[3] && chunks <= 4096; ++chunks) {
-            const int walk = std::min((o[3] + chunks - 1) / chunks, 4096);
-            if (walk == last)
+        // Walks of equal length, the last one shorter; virtual nodes halve the
+        // t extent, which leaves few of those, so there every length counts
+        // (two-row links 40^2 x 32^2 in 16 nodes: walks of 7 175 us, the best
+        // of 6 188; lexicographic fields lose by it, FP64 40^4 577 against 529).
+        for (int walk = std::min(o[3], 4096); walk > 0; --walk) {
+            const int chunks = (o[3] + walk - 1) / walk;
+            if (!vn && walk != (o[3] + chunks - 1) / chunks)
                 continue;
-            last = walk;
             const double us = dslash_walk_us(sh, prec, o, walk, cus);
             if (us < best) {
                 best = us;
                 c.schedule = sched;
                 c.tile_sites = walk;
+                c.xcd_remap = dslash_ranges(sh, o, walk, cus, dslash_per_cu(sh, prec)) ? 2 : 0;
             }
         }
     }
