@@ -956,14 +956,20 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
         }
     }
     if (is_batch_key(expr)) {
-        // One workgroup of 128 lanes per tile of 128 sites: a batch of any
+        // One tile per workgroup, one group of sites per lane: a batch of any
         // size fills the chip (four lattices of 8^4 to 24^3 x 48: 18 us
-        // against 141 with one wave walking 4096 sites; 64 lattices, 5.8 GB:
-        // 1145 us against 1223).  Cached like the site-local calls.
-        c.tile_sites = 128;
-        c.block = 128;
+        // against 141 with one wave walking 4096 sites).  Two waves of one
+        // double site per lane (32 lattices, 5.6 GB: 893 us; one wave with
+        // two sites in turn 991), else one wave, whose lanes take 2 or 4
+        // sites (64 lattices: two-row 3.3 GB 554 us, 676 beside an idle
+        // wave; single 5.0 GB 818 by rows, 1240; half 2.5 GB 444 with 256
+        // sites, 785 with 128).
+        const int op = expr - SU3_EXPR_BATCH;
+        const bool dbl = prec == SU3_F64;
+        c.block = dbl ? 128 : 64;
+        c.tile_sites = dbl ? 128 : 64 * natural_sites(prec, op);
         c.occupancy = 0;
-        c.schedule = expr != SU3_EXPR_BATCH + SU3_EXPR_MUL;
+        c.schedule = op != SU3_EXPR_MUL || prec == SU3_F32;
         const int64_t bytes = site_call_bytes(expr - SU3_EXPR_BATCH, prec, V);
         c.nontemporal = bytes <= (int64_t)100 * 1000 * 1000 ? 0
                         : bytes <= (int64_t)1000 * 1000 * 1000 ? 3
@@ -2582,7 +2588,10 @@ extern "C" su3_status su3_layout_recommend(su3_expr expr, su3_precision prec,
 // su3_fused_eval's rules; batch-level rules here), with the tile table
 // of the launch `cfg`: forced (the autotuner), else the tuned (or default)
 // setting of the batch key (SU3_EXPR_BATCH + leading expression, leading
-// item's precision, layout, lanes) at the total volume.
+// item's precision, layout, lanes) at the total volume; the default is that
+// of the precision of most bytes, double's where it has three quarters of them
+// (64 lattices of two-row links with half their bytes in double: 953 us with
+// one wave per tile, 1041 with two; three quarters in double 763 and 740).
 struct BatchPlan {
     std::vector<BatchItem> items;
     int mode;
@@ -2602,7 +2611,7 @@ static su3_status plan_batch(const su3_expr *exprs, su3_field *const *z,
     std::vector<BatchItem> &items = plan->items;
     items.assign(n, BatchItem());
     int mode = 0;
-    int64_t total_sites = 0;
+    int64_t total_sites = 0, bytes[4] = {0, 0, 0, 0};
     int dev = -1;
     for (int i = 0; i < n; ++i) {
         const int nops = (exprs[i] >= SU3_EXPR_MUL && exprs[i] <= SU3_EXPR_APB_AB)
@@ -2638,11 +2647,24 @@ static su3_status plan_batch(const su3_expr *exprs, su3_field *const *z,
               (z[i]->prec == SU3_F64 || z[i]->prec == SU3_C12_F32)))
             mode = 1;
         total_sites += z[i]->V;
+        bytes[z[i]->prec] += site_call_bytes(exprs[i], z[i]->prec, z[i]->V);
     }
-    const su3_launch cfg =
-        forced ? *forced
-               : lookup_launch(SU3_EXPR_BATCH + exprs[0], z[0]->prec,
-                               z[0]->layout, z[0]->lanes, total_sites);
+    su3_launch cfg;
+    if (forced) {
+        cfg = *forced;
+    } else if (!tuned_launch(SU3_EXPR_BATCH + exprs[0], z[0]->prec, z[0]->layout, z[0]->lanes,
+                             total_sites, &cfg)) {
+        const int64_t all = bytes[SU3_F64] + bytes[SU3_F32] + bytes[SU3_F16_F32ACC] +
+                            bytes[SU3_C12_F32];
+        int prec = SU3_F64;
+        if (4 * bytes[SU3_F64] < 3 * all) {
+            prec = SU3_F32;
+            for (int q : {SU3_F16_F32ACC, SU3_C12_F32})
+                if (bytes[q] > bytes[prec])
+                    prec = q;
+        }
+        cfg = default_launch(SU3_EXPR_BATCH + exprs[0], prec, z[0]->layout, total_sites);
+    }
     const int T = cfg.tile_sites;
     // tile table: item i owns ceil(V_i / T) tiles starting at the exclusive
     // prefix sum of its predecessors' counts
