@@ -600,9 +600,15 @@ static void release_stages()
         (void)hipFree(s.ptr);
 }
 
-// Fields of at least this many stored reals are converted on the device
-// (below, one thread packs them in less than the extra launch takes).
-static const int64_t kDeviceConvertReals = 8192;
+// Fields of at least this many stored reals are converted on the device;
+// below, one thread packs them in less than the extra launch takes.  In and
+// out takes 42 us and 0.018 a site on the device; on the host 22 us and 0.06 a
+// site in double (equal at 512 sites) and single (550), 0.11 in half (224),
+// 0.035 in two-row single (960).
+static int64_t device_convert_reals(int prec)
+{
+    return prec == SU3_F64 ? 9216 : prec == SU3_F32 ? 9900 : prec == SU3_F16_F32ACC ? 4032 : 11520;
+}
 
 // Run `part` over the canonical data of a field in pieces that fit a staging
 // buffer: part(order of the piece, its first host double, its bytes).
@@ -613,7 +619,7 @@ template <class F>
 static bool convert_on_device(const su3_field *f, hipStream_t hs, F part, su3_status *st)
 {
     int dev = -1;
-    if (f->V * f->E * f->ncomp < kDeviceConvertReals || hipGetDevice(&dev) != hipSuccess ||
+    if (f->V * f->E * f->ncomp < device_convert_reals(f->prec) || hipGetDevice(&dev) != hipSuccess ||
         dev != f->device)
         return false;
     const int64_t site_doubles = (int64_t)f->canon * f->ncomp;
@@ -669,6 +675,8 @@ struct Populate {
 #ifdef MADV_POPULATE_WRITE
         const size_t piece = (size_t)4 << 20;
         const size_t pieces = bytes / piece;
+        if (pieces < 2)
+            return;  // before a question to the system: 2.5 us of a small call's 36
         const size_t cpus = std::max(1u, std::thread::hardware_concurrency() / 2);
         const size_t n = std::min(std::min<size_t>(8, cpus), pieces / 2);
         const size_t page = (size_t)sysconf(_SC_PAGESIZE);
