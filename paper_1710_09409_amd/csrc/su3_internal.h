@@ -74,6 +74,7 @@ struct ShiftArgs {
     uint32_t nlanes;  // virtual nodes along the direction (1: none)
     uint32_t lstride; // lanes between virtual-node neighbours
     uint32_t lmask;   // N_sub - 1 (0 outside the virtual-node layout)
+    int32_t xcd_remap;
 };
 
 // One item of a batched launch (device-resident table).  The item owns

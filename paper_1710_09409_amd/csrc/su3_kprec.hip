@@ -56,13 +56,16 @@ __global__ __launch_bounds__(MAXB) void k_site(su3i::SiteArgs a)
 // site per lane: the lane of site s reads y at the neighbour s' of s along
 // one direction, periodic.  Consecutive lanes read consecutive sites of
 // the neighbouring row/plane, so the gather stays coalesced except at the
-// wrap of the shifted coordinate.
+// wrap of the shifted coordinate.  Bound by memory (FP64 48^4 product 352 us,
+// floor 340); 16 bytes per lane in single and half gained nothing (FP32 48^4
+// 200 us with two sites per lane, 197 with one).
 template <int MODE, int NT, int SCHED>
 __global__ __launch_bounds__(kMaxSiteBlock) void k_shift(su3i::ShiftArgs a)
 {
     extern __shared__ char occupancy_reserve[];
     constexpr int E = PrecT<P>::E;
-    const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t b = a.xcd_remap ? (uint32_t)xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t s = b * blockDim.x + threadIdx.x;
     if (s < (uint32_t)a.nsites) {
         // coordinate along the direction: outer part o, lane part l
         const uint32_t o = (s / a.stride) % a.extent;
