@@ -24,7 +24,7 @@ Prints ONE JSON line on stdout (progress and launch settings go to stderr):
                the Wilson hopping term, Grid's virtual-node layout,
                expression programs, fused vs chained expressions at 32^4
                (hot and cold) and the 64-lattice batch (persistent and
-               one-shot grids, graph replays; 64 small lattices batched
+               one-shot grids, launched again and again; 64 small lattices batched
                against separate launches); each variant time is the
                median over --repeats blocks of K launches (default 5)
 
@@ -645,8 +645,8 @@ def section_dslash(ctx):
 
 
 def section_batch(ctx):
-    """64 uneven lattices, mixed FP64 and compressed FP32, replayed from one
-    HIP graph: the tuned launch, the best persistent grid (k workgroups per
+    """64 uneven lattices, mixed FP64 and compressed FP32, launched as one
+    batch: the tuned launch, the best persistent grid (k workgroups per
     compute unit looping over the tiles), and 64 separate launches."""
     su3, testgen, stream, timer, make, tune = (ctx[k] for k in (
         "su3", "testgen", "stream", "timer", "make", "tune"))
