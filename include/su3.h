@@ -425,8 +425,8 @@ su3_status su3_program_info(const su3_program *p, su3_kind *result_kind,
  * (tuned or set) applies to programs with matrix values and a matrix result
  * (workgroups of three waves ignore its block), that of
  * SU3_EXPR_PROGRAM_SCALAR to programs with matrix values and a real or complex
- * result; a call without one takes cached or streaming loads and its occupancy
- * cap by its bytes and layout.  Programs without a matrix value take only its
+ * result; a call without one takes cached or streaming loads, its occupancy
+ * cap and XCD ranges by its bytes and layout.  Programs without a matrix value take only its
  * nontemporal bits and run 256-lane workgroups with no occupancy cap. */
 su3_status su3_program_eval(const su3_program *p, su3_field *z,
                             const su3_field *const *ops, int32_t n_ops,

@@ -390,7 +390,8 @@ template <class T, int NE, int NR, int NT>
 __global__ __launch_bounds__(256) void k_program(ProgArgs a)
 {
     extern __shared__ char occupancy_reserve[];
-    const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t group = a.xcd_remap ? (uint32_t)xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t s = group * blockDim.x + threadIdx.x;
     if (s < (uint32_t)a.nsites) {
         RegFile<T, NE, NR> R;
         load_all<T, NE, NR, NT>(a, s, R);
@@ -467,7 +468,7 @@ __global__ __launch_bounds__(256) void k_program(ProgArgs a)
 // kernel.  What bounds it is the latency of LDS and memory those waves hide:
 // a six-slot program holds the values no other wave reads in registers and
 // so fits four slots.  Measured, one-lane kernel and here:
-// (a*b+c*d)*(a*c+b*d)+(a-b)*(c-d) FP64 32^4 303 -> 222 us (755 MB), 8^4 18.6
+// (a*b+c*d)*(a*c+b*d)+(a-b)*(c-d) FP64 32^4 303 -> 219 us (755 MB), 8^4 18.6
 // -> 9.1, FP32 48^4 560 -> 517; a*b-adj(b)*adj(a) FP64 48^4 494 -> 369 (6.2
 // TB/s), FP32 16^4 7.1 -> 5.7; trace(a*b*adj(c)*adj(d)) FP64 48^4 660 -> 553.
 // The last result is also in the accumulator Z.  A product reads its right
@@ -826,7 +827,8 @@ __global__ __launch_bounds__(3 * kRowLanes) void k_program_rows(su3i::RowArgs a)
     f.own = slots + 3 * row * kRowEntry + lane;
     f.all = slots + lane;
     f.row = row;
-    const uint32_t first = blockIdx.x * (kRowLanes * S);  // the workgroup's first site
+    const uint32_t group = a.xcd_remap ? (uint32_t)xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t first = group * (kRowLanes * S);  // the workgroup's first site
     const uint32_t s0 = first + lane * S;
     const bool inside = s0 < (uint32_t)a.nsites;  // lanes past the end only take part
     if constexpr (AOS)

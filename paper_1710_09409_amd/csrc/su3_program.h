@@ -95,6 +95,7 @@ struct ProgArgs {
     uint8_t zkind, zprec;
     uint8_t nops, ninstr, result;
     uint8_t used;                // bit k: operand k is read
+    uint8_t xcd_remap;           // matrix form: each XCD takes a range of workgroups
     int32_t nsites;
     double imm[kProgMaxImm][2];
     ProgInstr ins[kProgMaxInstr];
@@ -111,7 +112,7 @@ struct RowArgs {
     uint8_t kind[kProgMaxOps], prec[kProgMaxOps], slot[kProgMaxOps];
     uint8_t zkind, zprec, nops, used, ninstr, nslots;
     uint8_t held;  // the code uses the registers
-    uint8_t aos;
+    uint8_t aos, xcd_remap;
     int32_t nsites;
     double imm[kProgMaxImm][2];
     RowInstr ins[kProgMaxInstr];

@@ -108,3 +108,31 @@ def test_rows_in_place(text, lay, prec):
     su3.su3_program_eval(prog, fs[0], fs, s)
     su3.su3_sync(s)
     assert torch.equal(z.owner, fs[0].owner)
+
+
+@pytest.mark.parametrize("prec,dims,program", [
+    (F64, (16, 16, 16, 32), PATHS), (F64, (16, 16, 16, 32), PLAQUETTE),
+    (F32, (16, 16, 32, 32), PATHS), (F32, (16, 16, 32, 32), SCALED),  # by lanes, by rows
+])
+def test_ranges_per_xcd(prec, dims, program):
+    """Planes of 2 MiB: workgroups in ranges by default, the bits of a launch
+    that deals them one by one."""
+    s = torch.cuda.current_stream()
+    V = testgen.volume(dims)
+    text, kinds = program
+    fs = [_make(dims, prec, k, SOA, _host(V, k, i), s) for i, k in enumerate(kinds)]
+    prog = su3.Program(text, kinds)
+    rk = prog.info()["result_kind"]
+    key = su3.SU3_EXPR_PROGRAM if rk == M else su3.SU3_EXPR_PROGRAM_SCALAR
+    y, z = (_make(dims, prec, rk, SOA, None, s) for _ in range(2))
+    su3.su3_launch_reset()
+    default = su3.su3_launch_get(key, prec, SOA[0], 0, dims).as_dict()
+    assert default["xcd_remap"] == 1
+    su3.su3_program_eval(prog, z, fs, s)
+    su3.su3_launch_set(key, prec, SOA[0], 0, dims, dict(default, xcd_remap=0))
+    try:
+        su3.su3_program_eval(prog, y, fs, s)
+    finally:
+        su3.su3_launch_reset()
+    su3.su3_sync(s)
+    assert torch.equal(y.owner, z.owner)
