@@ -1891,15 +1891,6 @@ extern "C" su3_status su3_program_destroy(su3_program *p)
     return SU3_OK;
 }
 
-// The row form takes matrix programs on three waves, which meet at barriers.
-// A host build of this library runs a kernel's lanes one after another, where
-// only the larger lattices may take it.
-#ifdef __HIP__
-static const int64_t kProgRowsSites = 1;
-#else
-static const int64_t kProgRowsSites = 2048;
-#endif
-
 static int row_sites_per_lane(const su3_field *z, int arith)
 {
     return arith == SU3_F32 && z->L % 2 == 0 ? 2 : 1;
@@ -1911,7 +1902,7 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
 {
     const ProgCode &pc = p->code;
     const bool aos = z->layout == SU3_LAYOUT_AOS;
-    if (pc.rows.n == 0 || z->V < kProgRowsSites)
+    if (pc.rows.n == 0)
         return nullptr;
     // AoS matrices without a matrix to store: the one-lane kernel's cached
     // loads reach the rest of a site's record in the same lines (FP64 32^4

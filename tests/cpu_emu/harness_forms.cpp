@@ -1,0 +1,197 @@
+// Forms of the calls that only some sizes, layouts or launches reach, run on
+// the CPU (see harness.cpp): programs by rows (in place, eight slots, ragged
+// lattices), the hopping term with one wave per hop and on rows too long for
+// their tiles.  Prints "fails 0" on success.
+#include "su3.h"
+#include <cmath>
+#include <cstdio>
+#include <cstring>
+#include <string>
+#include <vector>
+#include <hip/hip_runtime.h>
+extern "C" {
+void su3gen_field(uint64_t seed, uint64_t field_id, int64_t s_begin, int64_t count, double *out);
+void su3gen_spinor(uint64_t seed, uint64_t field_id, int64_t s_begin, int64_t count, double *out);
+int oracle_roundtrip(int prec, const double *in, double *out, int64_t V);
+int oracle_dslash(const double *const *u, const double *in, double *out, const int32_t dims[4]);
+int oracle_eval_expr(const char *text, int nops, const int *kinds, const double *const *fields, double *out, int64_t V);
+}
+
+static int fails = 0;
+#define CHECK(cond, ...)         \
+    do {                         \
+        if (!(cond)) {           \
+            std::printf(__VA_ARGS__); \
+            std::printf("\n");   \
+            ++fails;             \
+        }                        \
+    } while (0)
+
+struct Lay {
+    int layout, lanes;  // lanes: AoSoA; virtual nodes: simd of t
+};
+static int64_t volume(const int *d) { return (int64_t)d[0] * d[1] * d[2] * d[3]; }
+static int reals_of(int kind) { return kind == SU3_KIND_MATRIX ? 18 : kind == SU3_KIND_SPINOR ? 24 : kind == SU3_KIND_COMPLEX ? 2 : 1; }
+
+static su3_field *make(const int *d, int prec, int kind, Lay l, const double *host)
+{
+    su3_field *f = nullptr;
+    su3_status st;
+    if (l.layout == SU3_LAYOUT_VNODE) {
+        const int simd[4] = {1, 1, 1, l.lanes};
+        st = su3_vnode_alloc(&f, d, (su3_precision)prec, (su3_kind)kind, simd);
+    } else if (kind == SU3_KIND_MATRIX) {
+        st = su3_field_alloc(&f, d, (su3_precision)prec, (su3_layout)l.layout, l.lanes);
+    } else if (kind == SU3_KIND_SPINOR) {
+        st = su3_spinor_alloc(&f, d, (su3_precision)prec, (su3_layout)l.layout, l.lanes);
+    } else {
+        st = su3_scalar_alloc(&f, d, (su3_precision)prec, (su3_layout)l.layout, l.lanes, (su3_kind)kind);
+    }
+    CHECK(st == SU3_OK, "alloc: %s", su3_last_error());
+    if (host)
+        CHECK(su3_field_upload(f, host, nullptr) == SU3_OK, "upload: %s", su3_last_error());
+    return f;
+}
+
+static std::vector<double> host_values(int64_t V, int kind, int id)
+{
+    std::vector<double> h(18 * V);
+    su3gen_field(21, 30 + id, 0, V, h.data());
+    h.resize(reals_of(kind) * V);
+    return h;
+}
+
+static std::vector<double> stored(const std::vector<double> &h, int64_t V, int kind, int prec)
+{
+    std::vector<double> q(h);
+    if (kind == SU3_KIND_MATRIX)
+        oracle_roundtrip(prec, h.data(), q.data(), V);
+    else if (prec != SU3_F64)
+        for (double &x : q)
+            x = (double)(float)x;
+    return q;
+}
+
+static const int M = SU3_KIND_MATRIX, R = SU3_KIND_REAL, C = SU3_KIND_COMPLEX;
+
+// Programs by rows: against the oracle, and in place (over operand 0) bit for
+// bit as out of place.
+static void programs()
+{
+    struct Ex { const char *text; int n; int kinds[8]; };
+    static const Ex exs[] = {
+        {"a*b", 2, {M, M}}, {"a*adj(b) - conj(a)", 2, {M, M}}, {"transpose(a)", 1, {M}},
+        {"(a*b+c*d)*(a*c+b*d)+(a-b)*(c-d)", 4, {M, M, M, M}},
+        {"a*b+c*d+e*f+g*h", 8, {M, M, M, M, M, M, M, M}},  // eight slots
+        {"a*b + c*a - d*b + 0.5", 4, {M, M, C, R}}, {"trace(a*b*adj(c)*adj(d))", 4, {M, M, M, M}},
+        {"real(trace(a*adj(b)))*c", 3, {M, M, R}}};
+    static const int lattices[][4] = {{3, 3, 3, 7}, {4, 4, 4, 2}, {5, 1, 1, 1}, {3, 5, 7, 9}};
+    static const Lay lays[] = {{SU3_LAYOUT_AOS, 0}, {SU3_LAYOUT_SOA, 0}, {SU3_LAYOUT_AOSOA, 8}, {SU3_LAYOUT_VNODE, 2}};
+    for (const auto &d : lattices)
+        for (const Lay &l : lays) {
+            if (l.layout == SU3_LAYOUT_VNODE && d[3] % l.lanes)
+                continue;
+            const int64_t V = volume(d);
+            for (int arith : {(int)SU3_F64, (int)SU3_F32, (int)SU3_C12_F32})
+                for (const Ex &ex : exs) {
+                    su3_program *p;
+                    su3_kind kinds[8], rk;
+                    for (int k = 0; k < ex.n; ++k) kinds[k] = (su3_kind)ex.kinds[k];
+                    if (su3_program_create(&p, ex.text, ex.n, kinds) != SU3_OK) { CHECK(false, "%s: %s", ex.text, su3_last_error()); continue; }
+                    su3_program_info(p, &rk, nullptr, nullptr);
+                    std::vector<su3_field *> f;
+                    std::vector<std::vector<double>> q;
+                    std::vector<const double *> qp;
+                    for (int k = 0; k < ex.n; ++k) {
+                        const int prec = ex.kinds[k] == M || arith == SU3_F64 ? arith : (int)SU3_F32;
+                        const std::vector<double> h = host_values(V, ex.kinds[k], k);
+                        f.push_back(make(d, prec, ex.kinds[k], l, h.data()));
+                        q.push_back(stored(h, V, ex.kinds[k], prec));
+                    }
+                    for (auto &x : q) qp.push_back(x.data());
+                    const int zprec = arith == SU3_F64 ? (int)SU3_F64 : (int)SU3_F32;
+                    su3_field *z = make(d, zprec, rk, l, nullptr);
+                    const int n = reals_of(rk);
+                    std::vector<double> want(18 * V), got(n * V), over(n * V);
+                    oracle_eval_expr(ex.text, ex.n, ex.kinds, qp.data(), want.data(), V);
+                    CHECK(su3_program_eval(p, z, f.data(), ex.n, nullptr) == SU3_OK, "%s: %s", ex.text, su3_last_error());
+                    if (l.layout != SU3_LAYOUT_AOS || rk == SU3_KIND_MATRIX) {
+                        const bool rows = blockDim.x == 192;  // three waves
+                        // (single with four slots: one lane per site)
+                        CHECK(rows || arith != SU3_F64, "%s, %lld sites: not by rows", ex.text, (long long)V);
+                    }
+                    su3_field_download(z, got.data(), nullptr);
+                    double err = 0, mag = 0;
+                    for (int64_t i = 0; i < n * V; ++i) { err = std::max(err, std::fabs(got[i] - want[i])); mag = std::max(mag, std::fabs(want[i])); }
+                    CHECK(err <= (arith == SU3_F64 ? 1e-13 : 2e-6) * (1 + mag), "%s arith %d layout %d V %lld: err %.3e", ex.text, arith, l.layout, (long long)V, err);
+                    if (rk == ex.kinds[0] && (arith != SU3_C12_F32 || rk != SU3_KIND_MATRIX)) {
+                        CHECK(su3_program_eval(p, f[0], f.data(), ex.n, nullptr) == SU3_OK, "%s in place: %s", ex.text, su3_last_error());
+                        su3_field_download(f[0], over.data(), nullptr);
+                        CHECK(std::memcmp(over.data(), got.data(), sizeof(double) * n * V) == 0, "%s arith %d layout %d: differs in place", ex.text, arith, l.layout);
+                    }
+                    su3_field_free(z);
+                    for (auto *x : f) su3_field_free(x);
+                    su3_program_destroy(p);
+                }
+        }
+    std::printf("programs by rows done\n");
+}
+
+// The hopping term: one wave per hop bit for bit as one lane per site, and
+// rows too long for their tiles (the schedule's fallbacks).
+static void hopping()
+{
+    struct Case { int d[4]; Lay l; };
+    static const Case cases[] = {
+        {{3, 5, 7, 2}, {SU3_LAYOUT_SOA, 0}}, {{4, 4, 2, 3}, {SU3_LAYOUT_AOS, 0}}, {{5, 3, 2, 6}, {SU3_LAYOUT_AOSOA, 8}},
+        {{4, 2, 6, 4}, {SU3_LAYOUT_VNODE, 2}}, {{130, 1, 2, 2}, {SU3_LAYOUT_SOA, 0}}, {{300, 1, 1, 2}, {SU3_LAYOUT_SOA, 0}}};
+    for (const Case &c : cases)
+        for (int lp : {(int)SU3_F64, (int)SU3_F32, (int)SU3_C12_F32}) {
+            const int64_t V = volume(c.d);
+            const int sp = lp == SU3_F64 ? (int)SU3_F64 : (int)SU3_F32;
+            std::vector<std::vector<double>> q;
+            const double *up[4];
+            su3_field *u[4];
+            for (int mu = 0; mu < 4; ++mu) {
+                const std::vector<double> h = host_values(V, M, mu);
+                u[mu] = make(c.d, lp, M, c.l, h.data());
+                q.push_back(stored(h, V, M, lp));
+            }
+            for (int mu = 0; mu < 4; ++mu) up[mu] = q[mu].data();
+            std::vector<double> in(24 * V), qin(24 * V), want(24 * V), plain(24 * V), got(24 * V);
+            su3gen_spinor(21, 77, 0, V, in.data());
+            for (int64_t i = 0; i < 24 * V; ++i) qin[i] = sp == SU3_F64 ? in[i] : (double)(float)in[i];
+            oracle_dslash(up, qin.data(), want.data(), c.d);
+            su3_field *fin = make(c.d, sp, SU3_KIND_SPINOR, c.l, in.data());
+            su3_field *out = make(c.d, sp, SU3_KIND_SPINOR, c.l, nullptr);
+            // block, persistent, nontemporal, xcd_remap, lds_stage, tile_sites,
+            // occupancy, schedule, sites_per_lane
+            static const su3_launch ls[] = {
+                {64, 0, 0, 0, 0, 1, 0, 0, 0}, {64, 0, 0, 0, 0, 1, 0, 0, 8}, {64, 0, 3, 1, 0, 1, 0, 0, 8},
+                {256, 0, 2, 0, 0, 2, 0, 16, 0}, {256, 0, 2, 1, 0, 3, 0, 17, 0}, {256, 0, 2, 2, 0, 1, 0, 12, 0},
+                {256, 0, 2, 0, 0, 2, 0, 28, 0}};
+            const int lanes = c.l.layout == SU3_LAYOUT_AOSOA || c.l.layout == SU3_LAYOUT_VNODE ? c.l.lanes : 0;
+            for (const su3_launch &s : ls) {
+                CHECK(su3_launch_set(SU3_EXPR_DSLASH, (su3_precision)lp, (su3_layout)c.l.layout, lanes, c.d, &s) == SU3_OK, "launch: %s", su3_last_error());
+                CHECK(su3_dslash(out, u, fin, nullptr) == SU3_OK, "dslash: %s", su3_last_error());
+                CHECK(s.sites_per_lane != 8 || blockDim.x == 512, "not one wave per hop");
+                su3_field_download(out, &s == ls ? plain.data() : got.data(), nullptr);
+                CHECK(&s == ls || std::memcmp(plain.data(), got.data(), sizeof(double) * 24 * V) == 0, "dslash %dx%dx%dx%d layout %d prec %d: launch %d differs", c.d[0], c.d[1], c.d[2], c.d[3], c.l.layout, lp, (int)(&s - ls));
+            }
+            su3_launch_reset();
+            double err = 0;
+            for (int64_t i = 0; i < 24 * V; ++i) err = std::max(err, std::fabs(plain[i] - want[i]));
+            CHECK(err <= (sp == SU3_F64 ? 1e-13 : 2e-5), "dslash err %.3e", err);
+            su3_field_free(fin); su3_field_free(out);
+            for (int mu = 0; mu < 4; ++mu) su3_field_free(u[mu]);
+        }
+    std::printf("hopping term done\n");
+}
+
+int main()
+{
+    programs();
+    hopping();
+    std::printf("fails %d\n", fails);
+    return fails != 0;
+}

@@ -2,9 +2,11 @@
 // the library's kernels and C ABI can be compiled as ordinary C++ and run on
 // the CPU under AddressSanitizer/UBSan (test infrastructure only; the
 // product is never built against it).  A kernel launch runs every
-// (workgroup, lane) of the grid in turn -- or, for kernels with barriers,
-// each workgroup's lanes as threads meeting at a std::barrier; device memory
-// is host memory, streams are no-ops, graph capture records the launches.
+// (workgroup, lane) of the grid in turn; a lane that reaches a barrier waits
+// there, on a stack of its own, until the rest of its workgroup has come.  A
+// launch may touch the dynamic LDS it asked for and
+// no more.  Device memory is host memory, streams are no-ops, graph capture
+// records the launches.
 #pragma once
 #include <cstddef>
 #include <cstdint>
@@ -13,8 +15,6 @@
 #include <cstdio>
 #include <functional>
 #include <vector>
-#include <thread>
-#include <barrier>
 #include <algorithm>
 
 #define __global__
@@ -76,8 +76,12 @@ struct dim3 { unsigned x, y, z; dim3(unsigned a = 1, unsigned b = 1, unsigned c 
 struct emu_idx { unsigned x, y, z; };
 extern thread_local emu_idx blockIdx, threadIdx;
 extern emu_idx blockDim, gridDim;
-extern std::barrier<> *emu_bar;
-inline void __syncthreads() { if (emu_bar) emu_bar->arrive_and_wait(); }
+void emu_wait();  // a lane of a workgroup run in turn: at a barrier
+inline void __syncthreads() { emu_wait(); }
+// Run the lanes 0 .. lanes - 1 of a workgroup, each body(lane), between
+// barriers one after another.
+void emu_workgroup(unsigned lanes, const std::function<void(unsigned)> &body);
+void emu_lds_limit(size_t bytes);  // the dynamic LDS that a launch may touch
 using std::min;
 using std::max;
 
@@ -85,39 +89,19 @@ extern bool emu_capturing;
 extern std::vector<std::function<void()>> emu_graph;
 extern unsigned char emu_lds[1 << 18];
 extern int emu_launches;
-extern bool emu_threaded;  // run each block's threads as OS threads (barriers)
+extern bool emu_threaded;  // set around kernels with barriers; every launch can wait at them
 
 template <class K, class... A>
-inline void emu_run(K k, dim3 g, dim3 b, A... a)
+inline void emu_run(K k, dim3 g, dim3 b, size_t shm, A... a)
 {
     emu_launches++;
+    emu_lds_limit(shm);
     gridDim = {g.x, 1, 1};
     blockDim = {b.x, 1, 1};
-    if (emu_threaded) {
-        // one thread per lane for the whole launch; the workgroups run one
-        // after another, all lanes meeting at a barrier between them
-        std::barrier<> bar(b.x);
-        emu_bar = &bar;
-        std::vector<std::thread> th;
-        for (unsigned t = 0; t < b.x; ++t)
-            th.emplace_back([=, &bar]() {
-                for (unsigned bi = 0; bi < g.x; ++bi) {
-                    blockIdx = {bi, 0, 0};
-                    threadIdx = {t, 0, 0};
-                    k(a...);
-                    bar.arrive_and_wait();
-                }
-            });
-        for (auto &x : th) x.join();
-        emu_bar = nullptr;
-        return;
+    for (unsigned bi = 0; bi < g.x; ++bi) {
+        blockIdx = {bi, 0, 0};
+        emu_workgroup(b.x, [&](unsigned) { k(a...); });
     }
-    for (unsigned bi = 0; bi < g.x; ++bi)
-        for (unsigned t = 0; t < b.x; ++t) {
-            blockIdx = {bi, 0, 0};
-            threadIdx = {t, 0, 0};
-            k(a...);
-        }
 }
 
 template <class K, class... A>
@@ -128,9 +112,9 @@ inline void emu_launch(K k, dim3 g, dim3 b, size_t shm, A... a)
         std::abort();
     }
     if (emu_capturing)
-        emu_graph.push_back([=]() { emu_run(k, g, b, a...); });
+        emu_graph.push_back([=]() { emu_run(k, g, b, shm, a...); });
     else
-        emu_run(k, g, b, a...);
+        emu_run(k, g, b, shm, a...);
 }
 #define hipLaunchKernelGGL(K, G, B, SHM, ST, ...) emu_launch(K, G, B, SHM, __VA_ARGS__)
 
