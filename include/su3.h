@@ -497,7 +497,10 @@ su3_status su3_batch_run(const su3_expr *exprs, su3_field *const *z,
 
 /* Evaluate the batch once on `stream` (asynchronous, one kernel launch; it
  * can be captured): one pass of Section 3, Listing 1's site loop over every
- * item. */
+ * item.  Launches of one batch may be issued to several streams and by
+ * several threads; with a persistent grid each waits for the one before it
+ * (captured ones, whose graphs nothing orders, take tiles without the shared
+ * counter). */
 su3_status su3_batch_launch(su3_batch *b, void *stream);
 
 /* Release a batch (the batch of Section 3's site loop over several

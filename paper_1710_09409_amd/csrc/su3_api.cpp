@@ -62,6 +62,10 @@ struct su3_batch {
     su3_launch cfg;
     int32_t grid;
     int32_t device;
+    // persistent grids: launches draw their tiles from the one counter, so
+    // each waits for the one before it
+    std::mutex mu;
+    hipEvent_t last;  // recorded behind every launch that draws tickets
 };
 
 // ------------------------------------------------------------- errors
@@ -2726,7 +2730,6 @@ static su3_status batch_create(su3_batch **out, const su3_expr *exprs,
     const int64_t ntiles = plan.ntiles;
     const su3_launch cfg = plan.cfg;
     su3_batch *b = new su3_batch();
-    std::memset(b, 0, sizeof *b);
     b->nitems = n;
     b->ntiles = (int32_t)ntiles;
     b->mode = mode;
@@ -2749,6 +2752,8 @@ static su3_status batch_create(su3_batch **out, const su3_expr *exprs,
     }
     if (e == hipSuccess)
         e = hipStreamSynchronize(hs);
+    if (e == hipSuccess && b->d_queue)
+        e = hipEventCreateWithFlags(&b->last, hipEventDisableTiming);
     if (e != hipSuccess) {
         su3_status r = hip_fail(e, "batch create");
         su3_batch_destroy(b);
@@ -2841,13 +2846,32 @@ extern "C" su3_status su3_batch_launch(su3_batch *b, void *stream)
 {
     if (!b)
         return fail(SU3_ERR_INVALID_ARG, "batch is NULL");
+    hipStream_t hs = static_cast<hipStream_t>(stream);
+    unsigned long long *queue = b->d_queue;
+    if (queue) {
+        // nothing orders a captured launch against others of this batch when
+        // its graph runs: it strides over the tiles without the counter
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(hs, &capture) != hipSuccess) {
+            (void)hipGetLastError();
+            queue = nullptr;
+        } else if (capture != hipStreamCaptureStatusNone) {
+            queue = nullptr;
+        }
+    }
+    std::unique_lock<std::mutex> lock(b->mu, std::defer_lock);
+    if (queue) {
+        lock.lock();
+        HIP_TRY(hipStreamWaitEvent(hs, b->last, 0), "batch order");
+    }
     // one kernel: launched directly it costs 2.8 us of a stream's time, as a
     // graph of one node 15.3 us (either replayed back to back)
-    const hipError_t e =
+    hipError_t e =
         launch_batch(b->mode, b->d_items, b->nitems, b->ntiles, b->cfg.tile_sites,
                      b->cfg.nontemporal, b->cfg.schedule, b->cfg.block, b->grid,
-                     occupancy_reserve(b->device, b->cfg.occupancy), b->d_queue,
-                     static_cast<hipStream_t>(stream));
+                     occupancy_reserve(b->device, b->cfg.occupancy), queue, hs);
+    if (e == hipSuccess && queue)
+        e = hipEventRecord(b->last, hs);
     if (e != hipSuccess)
         return hip_fail(e, "batch launch");
     return SU3_OK;
@@ -2857,6 +2881,8 @@ extern "C" su3_status su3_batch_destroy(su3_batch *b)
 {
     if (!b)
         return SU3_OK;
+    if (b->last)
+        (void)hipEventDestroy(b->last);
     if (b->d_mem)
         (void)hipFree(b->d_mem);
     delete b;

@@ -120,7 +120,8 @@ __device__ __forceinline__ void batch_tile(const BatchItem *items, int nitems, i
 //     workgroup draws once more after its last tile, so a launch draws
 //     exactly ntiles + G tickets and leaves the counter at the next
 //     multiple of it: the queue never needs resetting between launches of
-//     the same batch (it starts at 0).  The next ticket is drawn while the
+//     the same batch (it starts at 0; launches must not overlap, which the
+//     host sees to).  The next ticket is drawn while the
 //     current tile is evaluated, so its latency is hidden.  The ticket goes
 //     from lane 0 to the workgroup through the first bytes of the dynamic
 //     LDS (the host reserves at least 16).

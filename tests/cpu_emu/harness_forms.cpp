@@ -1,7 +1,7 @@
 // Forms of the calls that only some sizes, layouts or launches reach, run on
 // the CPU (see harness.cpp): programs by rows (in place, eight slots, ragged
 // lattices), the hopping term with one wave per hop and on rows too long for
-// their tiles.  Prints "fails 0" on success.
+// their tiles, overlapping launches of a batch.  Prints "fails 0" on success.
 #include "su3.h"
 #include <cmath>
 #include <cstdio>
@@ -188,10 +188,73 @@ static void hopping()
     std::printf("hopping term done\n");
 }
 
+// Launches of one batch with a persistent grid share its ticket counter: on
+// any streams each waits for the event recorded behind the one before it, and
+// captured ones, which nothing orders, draw no tickets.
+static void batches()
+{
+    const int d[4] = {5, 6, 7, 8};
+    const Lay l = {SU3_LAYOUT_SOA, 0};
+    const int64_t V = volume(d);
+    const std::vector<double> hx = host_values(V, M, 0), hy = host_values(V, M, 1);
+    su3_field *x = make(d, SU3_F64, M, l, hx.data()), *y = make(d, SU3_F64, M, l, hy.data());
+    su3_field *z = make(d, SU3_F64, M, l, nullptr), *ref = make(d, SU3_F64, M, l, nullptr);
+    su3_mult(ref, x, y, nullptr);
+    std::vector<double> want(18 * V), got(18 * V);
+    su3_field_download(ref, want.data(), nullptr);
+    const su3_launch s = {64, 2, 3, 0, 0, 64, 0, 0, 0};
+    su3_launch_set((su3_expr)(SU3_EXPR_BATCH + SU3_EXPR_MUL), SU3_F64, SU3_LAYOUT_SOA, 0, d, &s);
+    const su3_expr ex = SU3_EXPR_MUL;
+    const su3_field *ops[4] = {x, y, nullptr, nullptr};
+    su3_batch *b = nullptr;
+    CHECK(su3_batch_create(&b, &ex, &z, ops, 1, nullptr) == SU3_OK, "batch: %s", su3_last_error());
+    const std::vector<double> zero(18 * V, 0.0);
+    const auto same = [&](const char *what) {
+        su3_field_download(z, got.data(), nullptr);
+        CHECK(std::memcmp(got.data(), want.data(), sizeof(double) * 18 * V) == 0, "batch %s: wrong result", what);
+        su3_field_upload(z, zero.data(), nullptr);
+    };
+    hipEvent_t last = nullptr;
+    for (uintptr_t stream : {1, 2, 2, 1, 3}) {
+        emu_calls.clear();
+        CHECK(su3_batch_launch(b, (void *)stream) == SU3_OK, "batch launch: %s", su3_last_error());
+        size_t launch = 0;
+        while (launch < emu_calls.size() && emu_calls[launch].what != 'L') ++launch;
+        bool waits = last == nullptr;
+        for (size_t i = 0; i < launch; ++i)
+            waits |= emu_calls[i].what == 'W' && emu_calls[i].event == last && emu_calls[i].stream == (void *)stream;
+        CHECK(waits, "batch on stream %d does not wait for the launch before it", (int)stream);
+        last = nullptr;
+        for (size_t i = launch; i < emu_calls.size(); ++i)
+            if (emu_calls[i].what == 'R' && emu_calls[i].stream == (void *)stream)
+                last = emu_calls[i].event;
+        CHECK(last != nullptr, "no event behind the batch");
+        same("launch");
+    }
+    hipGraph_t graph;
+    hipStreamBeginCapture((hipStream_t)4, hipStreamCaptureModeThreadLocal);
+    CHECK(su3_batch_launch(b, (void *)4) == SU3_OK, "batch capture: %s", su3_last_error());
+    hipStreamEndCapture((hipStream_t)4, &graph);
+    for (int rep = 0; rep < 3; ++rep) {
+        const int tickets = emu_atomics;
+        hipGraphLaunch((hipGraphExec_t)graph, nullptr);
+        CHECK(emu_atomics == tickets, "a captured batch draws tickets");
+        same("replay");
+        su3_batch_launch(b, nullptr);
+        same("between replays");
+    }
+    hipGraphDestroy(graph);
+    su3_batch_destroy(b);
+    su3_launch_reset();
+    for (su3_field *f : {x, y, z, ref}) su3_field_free(f);
+    std::printf("batches done\n");
+}
+
 int main()
 {
     programs();
     hopping();
+    batches();
     std::printf("fails %d\n", fails);
     return fails != 0;
 }

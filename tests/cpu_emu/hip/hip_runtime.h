@@ -47,8 +47,10 @@ inline void __builtin_amdgcn_sched_barrier(int) {}
 struct emu_buffer_rsrc { char *base; uint32_t records; };
 typedef emu_buffer_rsrc __amdgpu_buffer_rsrc_t;
 inline uint32_t __builtin_amdgcn_readfirstlane(uint32_t v) { return v; }
+extern int emu_atomics;
 inline unsigned long long atomicAdd(unsigned long long *p, unsigned long long v)
 {
+    ++emu_atomics;
     return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST);
 }
 inline emu_buffer_rsrc __builtin_amdgcn_make_buffer_rsrc(void *p, short, int records, int)
@@ -116,7 +118,10 @@ inline void emu_launch(K k, dim3 g, dim3 b, size_t shm, A... a)
     else
         emu_run(k, g, b, shm, a...);
 }
-#define hipLaunchKernelGGL(K, G, B, SHM, ST, ...) emu_launch(K, G, B, SHM, __VA_ARGS__)
+// What reached the streams, in order: 'L'aunches, event 'R'ecords and 'W'aits.
+struct emu_call { char what; hipStream_t stream; hipEvent_t event; };
+extern std::vector<emu_call> emu_calls;
+#define hipLaunchKernelGGL(K, G, B, SHM, ST, ...) (emu_calls.push_back({'L', ST, nullptr}), emu_launch(K, G, B, SHM, __VA_ARGS__))
 
 #define HIP_SYMBOL(x) (reinterpret_cast<const void *>(&(x)))
 inline hipError_t hipGetSymbolAddress(void **p, const void *symbol) { *p = const_cast<void *>(symbol); return hipSuccess; }
@@ -136,7 +141,12 @@ inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *
 inline hipError_t hipDeviceGetAttribute(int *v, int a, int) { *v = a == 1 ? 3 : (a == 2 ? 160 * 1024 : 64 * 1024); return hipSuccess; }
 inline hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { std::strcpy(p->gcnArchName, "emu"); p->multiProcessorCount = 3; return hipSuccess; }
 inline hipError_t hipEventCreate(hipEvent_t *e) { *e = nullptr; return hipSuccess; }
-inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+enum { hipEventDisableTiming = 2 };
+inline hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { static char n[1 << 12]; static int k = 0; *e = &n[k++ % (1 << 12)]; return hipSuccess; }
+inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { emu_calls.push_back({'R', s, e}); return hipSuccess; }
+inline hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { emu_calls.push_back({'W', s, e}); return hipSuccess; }
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
+inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *c) { *c = emu_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 inline hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
 inline hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 inline hipError_t hipStreamCreateWithFlags(hipStream_t *s, int) { *s = (void *)1; return hipSuccess; }
