@@ -907,6 +907,7 @@ __global__ __launch_bounds__(3 * kRowLanes) void k_program_rows(su3i::RowArgs a)
 #pragma unroll
             for (int j = 0; j < 3; ++j)
                 unpack<T, S>(p[4 * j * kRowEntry], d.m[j]);
+            apply_mode<3>(in.am, d);
 #pragma unroll
             for (int q = 0; q < S; ++q)
                 Z.m[0][q] = {(d.m[0][q].re + d.m[1][q].re) + d.m[2][q].re,

@@ -405,12 +405,10 @@ struct RowGen {
             case F_TRACE: {
                 if (a.ty != T_MATRIX)
                     return a;
-                // the trace of a conjugate or negative is the trace's
-                const int mode = a.mode & (ROW_CONJ | ROW_NEG);
-                a.mode = 0;
-                Val t = emit(ROW_TRACE, a, a, T_COMPLEX);
-                t.mode = mode;
-                return t;
+                // conjugate and sign go to the terms, before they are
+                // summed: a sum that cancels is +0 either way
+                a.mode &= ROW_CONJ | ROW_NEG;
+                return emit(ROW_TRACE, a, a, T_COMPLEX);
             }
             case F_REAL:
                 return a.ty == T_COMPLEX ? emit(ROW_REAL, a, a, T_REAL) : a;

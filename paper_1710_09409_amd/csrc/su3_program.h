@@ -57,7 +57,7 @@ enum RowOp : uint8_t {
     ROW_MUL_MS,     // Z = A (matrix) * B (scalar)
     ROW_ADD_MS,     // Z = A (matrix) + B (scalar) I
     ROW_ADD_S, ROW_MUL_S,
-    ROW_TRACE,      // Z = trace(A) (A in a slot, no mode)
+    ROW_TRACE,      // Z = trace(A) (A in a slot, not transposed)
     ROW_REAL, ROW_IMAG,
 };
 constexpr int ROW_ACC = 0x80;   // source: the accumulator; + k: register k - 1

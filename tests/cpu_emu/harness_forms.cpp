@@ -137,6 +137,42 @@ static void programs()
     std::printf("programs by rows done\n");
 }
 
+// Traces of negatives and conjugates: each term changes its sign before the
+// sum, so sums that cancel keep the zero's sign.
+static void traces()
+{
+    static const char *const texts[] = {"trace(-a)", "trace(conj(a))", "trace(adj(-a))", "trace(transpose(-conj(a)))", "-trace(a)"};
+    const int d[4] = {3, 3, 3, 3};
+    const int64_t V = volume(d);
+    std::vector<double> h(18 * V), got(2 * V);
+    for (int64_t i = 0; i < 18 * V; ++i) h[i] = (double)((i * 7 + i / 18) % 3 - 1);  // -1, 0, 1
+    for (int prec : {(int)SU3_F64, (int)SU3_F32})
+        for (Lay l : {Lay{SU3_LAYOUT_SOA, 0}, Lay{SU3_LAYOUT_AOSOA, 16}})
+            for (const char *text : texts) {
+                su3_field *a = make(d, prec, M, l, h.data()), *z = make(d, prec, C, l, nullptr);
+                su3_program *p;
+                const su3_kind kind = SU3_KIND_MATRIX;
+                su3_program_create(&p, text, 1, &kind);
+                CHECK(su3_program_eval(p, z, &a, 1, nullptr) == SU3_OK, "%s: %s", text, su3_last_error());
+                su3_field_download(z, got.data(), nullptr);
+                const bool outside = text[0] == '-', neg = std::strchr(text, '-') && !outside;
+                const bool conj = std::strstr(text, "conj") || std::strstr(text, "adj");
+                int bad = 0;
+                for (int64_t s = 0; s < V; ++s)
+                    for (int c = 0; c < 2; ++c) {
+                        const double sign = neg != (conj && c == 1) ? -1.0 : 1.0;
+                        const double *m = &h[18 * s + c];
+                        double t = (sign * m[0] + sign * m[8]) + sign * m[16];
+                        if (outside) t = -t;
+                        bad += std::memcmp(&t, &got[2 * s + c], sizeof t) != 0;
+                    }
+                CHECK(bad == 0, "%s prec %d layout %d: %d reals differ in their bits", text, prec, l.layout, bad);
+                su3_program_destroy(p);
+                su3_field_free(a); su3_field_free(z);
+            }
+    std::printf("traces done\n");
+}
+
 // The hopping term: one wave per hop bit for bit as one lane per site, and
 // rows too long for their tiles (the schedule's fallbacks).
 static void hopping()
@@ -253,6 +289,7 @@ static void batches()
 int main()
 {
     programs();
+    traces();
     hopping();
     batches();
     std::printf("fails %d\n", fails);
