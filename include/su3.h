@@ -256,7 +256,11 @@ su3_status su3_field_wrap(su3_field **out, void *dev_ptr, size_t bytes,
                           su3_layout layout, int32_t lanes);
 
 /* Release a handle (and its memory if owning): the end of the lattice
- * object of Section 4, Listing 3.  NULL is accepted. */
+ * object of Section 4, Listing 3.  NULL is accepted.  A handle on borrowed
+ * memory makes no HIP call (it may end while a stream is captured).  Transfers
+ * keep up to four staging buffers of 16 MiB on the device; the free of the last
+ * handle, if that one owns its memory, gives them back, and so does an
+ * allocation that would fail otherwise. */
 su3_status su3_field_free(su3_field *f);
 
 /* Device address and size of a field's storage (the stored layouts of

@@ -260,6 +260,8 @@ extern "C" su3_status su3_spinor_bytes(const int32_t dims[4],
 
 static std::atomic<int64_t> g_live_fields{0};
 
+static void release_stages();
+
 static su3_field *new_handle(const int32_t dims[4], int prec, int layout,
                              int32_t lanes, const Shape &s, int kind,
                              const int32_t *simd = nullptr)
@@ -303,6 +305,11 @@ static su3_status alloc_of_kind(su3_field **out, const int32_t dims[4],
     HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
     void *p = nullptr;
     hipError_t e = hipMalloc(&p, s.bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        release_stages();  // what the transfers keep
+        e = hipMalloc(&p, s.bytes);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SU3_ERR_OUT_OF_MEMORY, "hipMalloc(%zu bytes): %s", s.bytes,
@@ -483,17 +490,18 @@ extern "C" su3_status su3_vnode_wrap(su3_field **out, void *dev_ptr,
                         kind, simd);
 }
 
-static void release_stages();
-
 extern "C" su3_status su3_field_free(su3_field *f)
 {
     if (!f)
         return SU3_OK;
     hipError_t e = hipSuccess;
-    if (f->owns && f->ptr)
+    const bool owns = f->owns && f->ptr;
+    if (owns)
         e = hipFree(f->ptr);
     delete f;
-    if (--g_live_fields == 0)
+    // a handle on borrowed memory makes no HIP call: its end may come while
+    // a stream is captured, which a hipFree would break
+    if (--g_live_fields == 0 && owns)
         release_stages();
     if (e != hipSuccess)
         return hip_fail(e, "hipFree");
@@ -547,7 +555,8 @@ static inline double get_real(const void *img, int prec, int64_t idx)
 // Device buffers that hold a part of a field's canonical data on its way to
 // or from the host.  A transfer holds one for itself until its stream is
 // done with it; up to kStagesKept of them wait for the next transfer (any
-// thread, any stream) and go back to the device with the last field.
+// thread, any stream).  They go back to the device when the last field is
+// freed, if it owns its memory, and when an allocation fails.
 struct Stage {
     void *ptr;
     size_t bytes;

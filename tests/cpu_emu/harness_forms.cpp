@@ -286,12 +286,52 @@ static void batches()
     std::printf("batches done\n");
 }
 
+// The transfers' staging buffers: a handle on borrowed memory ends without a
+// HIP call, the last owning one gives them back, and so does an allocation
+// that would fail.
+static void staging()
+{
+    const int d[4] = {8, 8, 8, 4};
+    const int64_t V = volume(d);
+    const Lay l = {SU3_LAYOUT_SOA, 0};
+    const std::vector<double> h = host_values(V, M, 0);
+    size_t bytes = 0;
+    su3_field_bytes(d, SU3_F64, SU3_LAYOUT_SOA, 0, &bytes);
+    void *mem = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+    const auto borrowed = [&]() {
+        su3_field *f = nullptr;
+        CHECK(su3_field_wrap(&f, mem, bytes, d, SU3_F64, SU3_LAYOUT_SOA, 0) == SU3_OK, "wrap: %s", su3_last_error());
+        CHECK(su3_field_upload(f, h.data(), nullptr) == SU3_OK, "upload: %s", su3_last_error());
+        const int frees = emu_frees;
+        su3_field_free(f);
+        CHECK(emu_frees == frees, "the end of a borrowed field frees device memory");
+    };
+    borrowed();
+    int frees = emu_frees;
+    su3_field *f = make(d, SU3_F64, M, l, h.data());
+    su3_field_free(f);
+    CHECK(emu_frees == frees + 2, "the last owning field keeps the staging buffer");
+    borrowed();
+    frees = emu_frees;
+    emu_failing_mallocs = 1;
+    CHECK(su3_field_alloc(&f, d, SU3_F64, SU3_LAYOUT_SOA, 0) == SU3_OK, "an allocation fails beside kept buffers: %s", su3_last_error());
+    CHECK(emu_frees == frees + 1, "no staging buffer given back");
+    emu_failing_mallocs = 2;
+    su3_field *g = nullptr;
+    CHECK(su3_field_alloc(&g, d, SU3_F64, SU3_LAYOUT_SOA, 0) == SU3_ERR_OUT_OF_MEMORY, "no memory, but a field");
+    emu_failing_mallocs = 0;
+    su3_field_free(f);
+    std::free(mem);
+    std::printf("staging done\n");
+}
+
 int main()
 {
     programs();
     traces();
     hopping();
     batches();
+    staging();
     std::printf("fails %d\n", fails);
     return fails != 0;
 }

@@ -128,8 +128,9 @@ inline hipError_t hipGetSymbolAddress(void **p, const void *symbol) { *p = const
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline const char *hipGetErrorString(hipError_t e) { return e ? "emu error" : "success"; }
 inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
-template <class Q> inline hipError_t hipMalloc(Q **pp, size_t n) { void **p = (void **)pp; *p = std::aligned_alloc(256, (n + 255) / 256 * 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
-inline hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
+extern int emu_failing_mallocs, emu_frees;  // allocations that fail from now on; frees so far
+template <class Q> inline hipError_t hipMalloc(Q **pp, size_t n) { if (emu_failing_mallocs > 0) { --emu_failing_mallocs; return hipErrorOutOfMemory; } void **p = (void **)pp; *p = std::aligned_alloc(256, (n + 255) / 256 * 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
+inline hipError_t hipFree(void *p) { ++emu_frees; std::free(p); return hipSuccess; }
 inline hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
 inline hipError_t hipMemsetD32Async(hipDeviceptr_t p, int v, size_t n, hipStream_t) { auto *q = (uint32_t *)p; for (size_t i = 0; i < n; ++i) q[i] = (uint32_t)v; return hipSuccess; }
 inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, int, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
