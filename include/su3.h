@@ -157,8 +157,10 @@ typedef struct su3_program su3_program;
  *               nontemporal at system scope, which move results to HBM
  *               faster than nontemporal stores on gfx950; values 0-3, 6, 7
  *               (su3_dslash and programs 0-3; su3_dslash: bit 0 applies to
- *               link loads only; the LDS-tiled walks always load cached,
- *               store nontemporal)
+ *               link loads only; the LDS-tiled walks take no heed of it:
+ *               they store nontemporal and load cached, but for the
+ *               t-links, each read once per walk, in layouts whose
+ *               lane-blocks hold whole 128-byte lines)
  *   xcd_remap   1: hand each of the 8 XCDs a contiguous range of
  *               workgroups instead of the hardware's round-robin;
  *               2 (su3_dslash's LDS-tiled walks): each XCD walks one

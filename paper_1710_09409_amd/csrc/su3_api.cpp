@@ -196,6 +196,12 @@ static int64_t storage_site(const su3_field *f, int64_t s)
     return osite * f->L + lane;
 }
 
+// Whether an entry of a lane-block fills whole 128-byte lines.
+static bool whole_lines(const su3_field *f)
+{
+    return f->layout == SU3_LAYOUT_SOA || f->L * 2 * f->rbytes >= 128;
+}
+
 static Geom geom_of(const su3_field *f)
 {
     Geom g;
@@ -1745,6 +1751,7 @@ static su3_status launch_dslash_op(su3_field *out, su3_field *const links[4],
     int64_t grid = (lanes + c.block - 1) / c.block;
     if (lds) {
         // LDS-tiled walk: tiles of (x, y, z) sites walking t
+        a.t_bypass = whole_lines(u0);
         a.lds_tile = (uint32_t)c.schedule;
         a.lds_tx = (uint32_t)sh.tx;
         a.walk = (uint32_t)std::min<int64_t>(std::max(c.tile_sites, 1), Lt);

@@ -44,6 +44,7 @@ struct DslashArgs {
     // 1: one wave per hop, kDslashHopSites sites in index order per
     // workgroup of kDslashHopBlock lanes (walk == 1, no tile)
     uint32_t hop_waves;
+    uint32_t t_bypass;  // LDS-tiled walks: t-links are not kept in the caches
 };
 
 constexpr int kDslashHopSites = 64;

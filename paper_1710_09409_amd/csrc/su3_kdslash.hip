@@ -734,6 +734,12 @@ constexpr int lds_min_waves()
     return SP == su3i::F64 ? 2 : (VN ? 3 : 4);
 }
 
+// NT: 2, or 6 where the walk's t-links bypass the caches.  Both t-hops of
+// such a link happen in one step, so it is not kept: the caches hold the other
+// links and the faces, which are read twice (FP64 48^4 1007 us cached, 988
+// bypassed).  Where a lane-block's entry is shorter than a 128-byte line a
+// bypassed line comes once per piece, so there they stay cached (N_sub 4 FP32
+// 48^4 704 us, bypassed 765; FP64 AoS 40^4 1242 and 1447).
 template <int SP, int LP, int NT, int TX, int TY, int TZ, int NB, bool VN, bool HALO>
 __global__ __launch_bounds__((lds_max_lanes<SP, TX, TY, TZ, VN>()), (lds_min_waves<SP, VN>()))
 void k_dslash_lds(su3i::DslashArgs a)
@@ -908,10 +914,7 @@ void k_dslash_lds(su3i::DslashArgs a)
                                             : r + V3 * (t + 1 == Lt ? 0 : t + 1);
                     Cx<T> p[4][3], m[9], h[2][3], w[2][3];
                     load_spinor<SP, NT & 2>(a.in, site_offset(a.gs, sp1), a.gs.plane, p);
-                    // both t-hops of this link happen here: it is not kept in
-                    // the caches, which the other links and faces are read
-                    // from twice (FP64 48^4 1007 us cached, 988 so)
-                    load_link<LP, 1>(a.u[3], site_offset(a.gl, s), a.gl.plane, m);
+                    load_link<LP, (NT >> 2) & 1>(a.u[3], site_offset(a.gl, s), a.gl.plane, m);
                     project<3, -1>(p, h);
                     color_mul<0>(m, h, w);
                     reconstruct<3, -1>(w, acc);
@@ -1068,8 +1071,9 @@ template <int SP, int LP>
 static hipError_t go(int nt, int block, int grid, size_t shm, const su3i::DslashArgs &a,
                      hipStream_t st)
 {
-    if (a.lds_tile)  // cached loads and nontemporal stores, whatever nt asks
-        return go_lds<SP, LP, 2>(block, grid, shm, a, st);
+    if (a.lds_tile)  // nontemporal stores, loads by the layout, whatever nt asks
+        return a.t_bypass ? go_lds<SP, LP, 6>(block, grid, shm, a, st)
+                          : go_lds<SP, LP, 2>(block, grid, shm, a, st);
     switch (nt & 3) {
     case 0:
         go_nt<SP, LP, 0>(block, grid, shm, a, st);

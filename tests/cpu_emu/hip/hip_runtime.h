@@ -71,6 +71,16 @@ inline void emu_buffer_store(V v, emu_buffer_rsrc r, uint32_t off, uint32_t soff
 #define __builtin_amdgcn_raw_buffer_store_b64(v, r, off, soff, aux) emu_buffer_store(v, r, off, soff)
 #define __builtin_amdgcn_raw_buffer_store_b32(v, r, off, soff, aux) emu_buffer_store(v, r, off, soff)
 #define __builtin_amdgcn_raw_buffer_store_b16(v, r, off, soff, aux) emu_buffer_store(v, r, off, soff)
+// Nontemporal loads from the watched range.
+extern const char *emu_watch_lo, *emu_watch_hi;
+extern long emu_watched;
+template <class V>
+inline V emu_nontemporal_load(const V *p)
+{
+    emu_watched += (const char *)p >= emu_watch_lo && (const char *)p < emu_watch_hi;
+    return *p;
+}
+#define __builtin_nontemporal_load(p) emu_nontemporal_load(p)
 struct hipPointerAttribute_t { int type; int device; };
 struct hipDeviceProp_t { char gcnArchName[64]; int multiProcessorCount; };
 
