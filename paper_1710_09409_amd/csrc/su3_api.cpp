@@ -1175,15 +1175,16 @@ static int dslash_per_cu(const LdsShape &sh, int prec)
 // share of the memory rate.  The last walk of each tile may be shorter; those
 // run last, beside the remaining long ones.  The constants are fitted to 44
 // measured lattices (24^4 to 64 x 32^3, odd extents, virtual nodes; up to 13
-// row tiles with up to 12 walks each): the plan runs within 1.1 % (double),
-// 0.6 % (single) and 1.5 % (two-row links) of the fastest on average, 4.4, 4.6
-// and 8.4 % at most.
+// row tiles with up to 12 walks each) and checked on 12 more in eight layouts
+// and three precisions: the planned launch takes 0.88 of the time of one fixed
+// schedule (double 17 in walks of 8, single 16 in walks of 7) on average and at
+// most 1.05.
 static double dslash_walk_us(const LdsShape &sh, int prec, const int32_t o[4],
                              int walk, int cus)
 {
     const bool dbl = prec == SU3_F64;
     const double spinor = dbl ? 192 : 96, link = dbl ? 144 : prec == SU3_F32 ? 72 : 48;
-    const double floor_us = dbl ? 12.0 : sh.nb == 2 ? 11.05 : 13.0;
+    const double floor_us = dbl ? 12.0 : sh.nb == 1 ? 13.0 : sh.nsub == 1 ? 10.4 : 10.2;
     const double start = 0.5, cu_bytes_per_us = 28e3;
     // bytes per site: links, input, output, and the share of the face sites'
     // second reads that miss (in double a halo saves some of those of a
@@ -1241,6 +1242,11 @@ static bool dslash_ranges(const LdsShape &sh, const int32_t o[4], int walk, int 
     const int64_t xcd = std::max(1, cus / 8 * per_cu), slots = std::max(1, cus * per_cu);
     if ((t8 * chunks + xcd - 1) / xcd > (n * chunks + slots - 1) / slots)
         return false;
+    // nor where it gives some CU one more workgroup (100 tiles in 5 walks, 65
+    // for the 32 CUs of an XCD: FP32 20 x 40^3 198 us, singly 141)
+    const int64_t cus_xcd = std::max(1, cus / 8), cus_all = std::max(1, cus);
+    if ((t8 * chunks + cus_xcd - 1) / cus_xcd > (n * chunks + cus_all - 1) / cus_all)
+        return false;
     double singly = 0, ranges = 0;
     for (int z = 0; z < nz; ++z)
         for (int y = 0; y < ny; ++y)
@@ -1276,23 +1282,39 @@ static su3_launch plan_dslash(int prec, int layout, int64_t L, const int32_t dim
     // double spinors lie site after site (174 against 148).
     // Single AoS spinors keep it at any size: the walks store nontemporally,
     // which AoS pays for (FP32 32^4: 238 us against 434).
-    const bool aos = layout == SU3_LAYOUT_AOS;
+    const bool aos = layout == SU3_LAYOUT_AOS, pairs = vn && nsub < 4;
     const int64_t most = aos && !dbl ? ((int64_t)1 << 31) : (aos || (vn && nsub < 8)) ? 150000 : 360000;
-    if (V <= most) {
-        c.schedule = 0;
-        c.tile_sites = 1;
-        c.sites_per_lane = 8;
-        c.xcd_remap = 1;
-        c.nontemporal = aos || (vn && nsub < 8) ? 0 : 2;
-        return c;
-    }
+    su3_launch hops = c;
+    hops.schedule = 0;
+    hops.tile_sites = 1;
+    hops.sites_per_lane = 8;
+    hops.xcd_remap = 1;
+    hops.nontemporal = aos || (vn && nsub < 8) ? 0 : 2;
+    if (V <= most)
+        return hops;
     double best = 1e300;
     // of equals the first: two buffers where the links are two-row (48^4 16/7
     // 454 us, 12/7 466), one otherwise (FP32 26 x 30 x 34 x 28 100 us, 103)
     static const int by_tile[] = {9, 10, 11, 12, 16, 17, 18, 20, 21, 22, 26, 27, 28};
     static const int by_buffers[] = {16, 18, 26, 28, 9, 10, 11, 12, 17, 20, 21, 22, 27};
+    LdsShape rows;
+    const int aos_rows = lds_shape(18, 256, cbytes, o[0], 1, rows) ? 18 : 17;
+    // Outer rows that no tile holds and that divide badly are cut into many
+    // pieces, whose walks the model takes for too fast: there 4 x 4 rows with
+    // two buffers and walks of 7 (N_sub 8 FP32 34^4, pieces of 2: 195 us, the
+    // model's 17/9 264).
+    const bool small = !dbl && V <= 700000 && !(pairs && prec == SU3_F32);
+    if (vn && !dbl && lds_shape(16, 256, cbytes, o[0], nsub, rows) && 12 * rows.tx < o[0])
+        return small ? hops : c;
     for (int sched : prec == SU3_C12_F32 ? by_buffers : by_tile) {
         LdsShape sh;
+        // Where a lane's line holds more of other entries than of its own,
+        // only two buffers, which read a slice ahead: double AoS in 3 x 3 rows
+        // (32^4 18/16 447 us, 22/8 512, 17/8 488), single with N_sub 2 (48^4
+        // 18/24 848 us, 17/24 1066, 16/7 986).
+        if ((aos && sched != aos_rows && sched != aos_rows + 10) ||
+            (pairs && !dbl && sched != 16 && sched != 18))
+            continue;
         if (!lds_shape(sched, 256, cbytes, o[0], nsub, sh))
             continue;
         // Walks of equal length, the last one shorter; virtual nodes halve the
@@ -1308,11 +1330,24 @@ static su3_launch plan_dslash(int prec, int layout, int64_t L, const int32_t dim
                 best = us;
                 c.schedule = sched;
                 c.tile_sites = walk;
-                c.xcd_remap = dslash_ranges(sh, o, walk, cus, dslash_per_cu(sh, prec)) ? 2 : 0;
+                // (singly where lines hold several entries: N_sub 2 FP64 48^4
+                // 1334 us, in ranges 1417; N_sub 4 44^4 830 and 871)
+                c.xcd_remap = !(vn && nsub < 8) &&
+                                      dslash_ranges(sh, o, walk, cus, dslash_per_cu(sh, prec))
+                                  ? 2
+                                  : 0;
             }
         }
     }
-    return c;
+    // Single spinors to 24^3 x 48 take one wave per hop where the walks suffer
+    // from the lattice's extents: a site's hops take 0.092 ns with two-row
+    // links and 0.108 with three rows (N_sub 16 28^4 55 us, walk 99; FP32 66
+    // and 82; FP32 26^4 49.5 and 65.6), but with N_sub 2 0.19 (28^4 119, 92).
+    // With virtual nodes, and on few t-slices, where a tile needs few walks,
+    // the model takes the walks for slower than they are.
+    const double hop_us = (prec == SU3_C12_F32 ? 0.092e-3 : 0.108e-3) * (double)V;
+    const double margin = vn || o[3] <= 16 ? 1.16 : 1.05;
+    return small && best > margin * hop_us ? hops : c;
 }
 
 // plan_dslash, remembered per lattice (a few microseconds of host time
