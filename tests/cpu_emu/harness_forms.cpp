@@ -225,40 +225,33 @@ static void hopping()
 }
 
 // The walks' t-links bypass the caches where a lane-block's entry fills whole
-// lines, and nowhere else: a bypassed line comes once per piece of it.
+// lines (a bypassed line comes once per piece of it) and the call does not fit
+// the Infinity Cache, and nowhere else.
 static void t_links()
 {
-    struct Case { int prec; Lay l; bool whole; };
+    struct Case { int prec; Lay l; int t; bool bypass; };
     static const Case cases[] = {
-        {SU3_F64, {SU3_LAYOUT_SOA, 0}, true}, {SU3_F32, {SU3_LAYOUT_SOA, 0}, true}, {SU3_F64, {SU3_LAYOUT_AOS, 0}, false},
-        {SU3_F64, {SU3_LAYOUT_AOSOA, 8}, true}, {SU3_F32, {SU3_LAYOUT_AOSOA, 8}, false}, {SU3_C12_F32, {SU3_LAYOUT_AOSOA, 8}, false},
-        {SU3_F32, {SU3_LAYOUT_AOSOA, 16}, true}, {SU3_F64, {SU3_LAYOUT_VNODE, 4}, false}, {SU3_F64, {SU3_LAYOUT_VNODE, 8}, true},
-        {SU3_F32, {SU3_LAYOUT_VNODE, 8}, false}, {SU3_C12_F32, {SU3_LAYOUT_VNODE, 16}, true}};
-    const int d[4] = {2, 3, 2, 32};
+        {SU3_F64, {SU3_LAYOUT_SOA, 0}, 1, false}, {SU3_F64, {SU3_LAYOUT_SOA, 0}, 4, true},
+        {SU3_F64, {SU3_LAYOUT_AOSOA, 8}, 4, true}, {SU3_F64, {SU3_LAYOUT_VNODE, 4}, 4, false}};
     for (const Case &c : cases) {
-        const int sp = c.prec == SU3_F64 ? (int)SU3_F64 : (int)SU3_F32;
-        const std::vector<double> h = host_values(volume(d), M, 0);
-        std::vector<double> in(24 * volume(d));
-        su3gen_spinor(21, 77, 0, volume(d), in.data());
-        su3_field *u[4], *fin = make(d, sp, SU3_KIND_SPINOR, c.l, in.data()), *out = make(d, sp, SU3_KIND_SPINOR, c.l, nullptr);
-        for (int mu = 0; mu < 4; ++mu) u[mu] = make(d, c.prec, M, c.l, h.data());
-        const int lanes = c.l.layout == SU3_LAYOUT_AOSOA || c.l.layout == SU3_LAYOUT_VNODE ? c.l.lanes : 0;
-        for (int sched : {9, 18}) {
-            const su3_launch s = {256, 0, 2, 0, 0, 2, 0, sched, 0};
-            CHECK(su3_launch_set(SU3_EXPR_DSLASH, (su3_precision)c.prec, (su3_layout)c.l.layout, lanes, d, &s) == SU3_OK, "launch: %s", su3_last_error());
-            void *p;
-            size_t n;
-            su3_field_data(u[3], &p, &n);
-            emu_watch_lo = (const char *)p;
-            emu_watch_hi = emu_watch_lo + n;
-            emu_watched = 0;
-            CHECK(su3_dslash(out, u, fin, nullptr) == SU3_OK, "dslash: %s", su3_last_error());
-            CHECK((emu_watched > 0) == c.whole, "prec %d layout %d/%d schedule %d: %ld t-link loads bypass the caches", c.prec, c.l.layout, c.l.lanes, sched, emu_watched);
-            emu_watch_lo = emu_watch_hi = nullptr;
-        }
+        const int d[4] = {48, 48, 48, c.t};  // 106 MB, 425 MB
+        su3_field *u = make(d, c.prec, M, c.l, nullptr);
+        su3_field *in = make(d, c.prec, SU3_KIND_SPINOR, c.l, nullptr), *out = make(d, c.prec, SU3_KIND_SPINOR, c.l, nullptr);
+        su3_field *links[4] = {u, u, u, u};
+        const int lanes = c.l.layout == SU3_LAYOUT_SOA ? 0 : c.l.lanes;
+        const su3_launch s = {256, 0, 2, 0, 0, 1, 0, 9, 0};
+        CHECK(su3_launch_set(SU3_EXPR_DSLASH, (su3_precision)c.prec, (su3_layout)c.l.layout, lanes, d, &s) == SU3_OK, "launch: %s", su3_last_error());
+        void *p;
+        size_t n;
+        su3_field_data(u, &p, &n);
+        emu_watch_lo = (const char *)p;
+        emu_watch_hi = emu_watch_lo + n;
+        emu_watched = 0;
+        CHECK(su3_dslash(out, links, in, nullptr) == SU3_OK, "dslash: %s", su3_last_error());
+        CHECK((emu_watched > 0) == c.bypass, "prec %d layout %d/%d t %d: %ld link loads bypass the caches", c.prec, c.l.layout, c.l.lanes, c.t, emu_watched);
+        emu_watch_lo = emu_watch_hi = nullptr;
         su3_launch_reset();
-        su3_field_free(fin); su3_field_free(out);
-        for (int mu = 0; mu < 4; ++mu) su3_field_free(u[mu]);
+        for (su3_field *f : {u, in, out}) su3_field_free(f);
     }
     std::printf("t-links done\n");
 }
