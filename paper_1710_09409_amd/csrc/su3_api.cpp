@@ -913,8 +913,8 @@ static int64_t site_call_bytes(int expr, int prec, int64_t V)
 static const int64_t kCachedBytes = (int64_t)160 * 1000 * 1000;
 
 // The launch of a call that nothing tuned or set: V sites of the key's
-// expression, precision and layout.
-static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
+// expression, precision, layout and lanes.
+static su3_launch default_launch(int expr, int prec, int layout, int lanes, int64_t V)
 {
     su3_launch c;
     c.block = 64;
@@ -927,6 +927,13 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
     c.schedule = layout == SU3_LAYOUT_AOS ? 0 : 1;
     c.sites_per_lane = 0;
     const bool site = expr >= SU3_EXPR_MUL && expr <= SU3_EXPR_APB_AB;
+    // Bytes of an entry in a lane-block.  Where it is shorter than a 128-byte
+    // line a nontemporal access takes the line once per piece, so calls on
+    // such layouts keep loads, and below 64 bytes stores, cached (N_sub 2 and
+    // 4, AoSoA-8).
+    const int64_t run = layout == SU3_LAYOUT_AOSOA || layout == SU3_LAYOUT_VNODE
+                            ? (int64_t)lanes * 2 * real_bytes(prec)
+                            : 1 << 20;
     if (site && layout == SU3_LAYOUT_AOS) {
         // Whole tiles through LDS: FP64 32^4 70 us, against 679 us read
         // directly, site by site.  Calls of up to kCachedBytes keep their
@@ -971,6 +978,22 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
             c.occupancy = dbl || (large && !half) ? 5 : 8;
             c.nontemporal = dbl || large ? 7 : 3;
         }
+        if (run < 64 && (bytes > kCachedBytes || run < 32 || !half)) {
+            // 5 waves per CU (FP32 N_sub 2 48^3 x 24 MUL: 133 us, with
+            // nontemporal accesses 419 to 489), 8 in small calls (half N_sub 2
+            // 24^4 ADD 11.2 us, 5 waves 12.3, loads cached alone 29.5); small
+            // half calls on pieces of 32 bytes take every wave (MUL3 24^4 8.5
+            // and 10.2)
+            c.occupancy = bytes > kCachedBytes || run == 16 ? 5 : 8;
+            c.nontemporal = 0;
+            c.schedule = 1;
+        } else if (run == 64 && bytes > kCachedBytes) {
+            c.occupancy = 5;
+            c.nontemporal = 2;
+            c.schedule = 1;
+        } else if (run < 256 && c.nontemporal == 7) {
+            c.nontemporal = 3;
+        }
         // Entry planes a multiple of 2 MiB apart (2 to 16 MiB: power-of-two
         // lattices) meet in the same memory channels: there each XCD takes a
         // range of its own (FP64 32^4 73 us against 81, 16^3 x 32 9.0 against
@@ -1001,6 +1024,10 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
         c.nontemporal = bytes <= (int64_t)100 * 1000 * 1000 ? 0
                         : bytes <= (int64_t)1000 * 1000 * 1000 ? 3
                                                                : 7;
+        // (12 lattices of 32^4, N_sub 4: single 652 us, streamed 1406; half 304
+        // and 1301; double 990 and 1155)
+        if (run <= 64)
+            c.nontemporal = 0;
     }
     if (expr == SU3_EXPR_CSHIFT || expr == SU3_EXPR_MUL_SHIFTED) {
         // One site per lane: 8 (single) or 4 bytes (half) per access instead
@@ -1031,6 +1058,15 @@ static su3_launch default_launch(int expr, int prec, int layout, int64_t V)
             c.block = 128;
             c.occupancy = bytes <= 64 * MB ? 5 : 3;
             c.nontemporal = bytes <= 64 * MB ? 0 : bytes <= 200 * MB ? 3 : 7;
+        }
+        if (run < 64 && bytes > 100 * MB) {
+            // (FP32 N_sub 2 48^3 x 24 copy 91 us, nontemporal loads 215 to 379)
+            c.block = product && run == 32 ? 128 : 256;
+            c.occupancy = product && run == 32 ? 3 : 4;
+            c.nontemporal = 2;
+            c.schedule = 0;
+        } else if (run <= 64 && dbl && bytes > 64 * MB) {
+            c.nontemporal = 2;
         }
         // Power-of-two planes, as for the site-local calls (FP64 32^4 product
         // 73 us against 87, copy 50 against 63; FP32 38 against 42; half copy
@@ -1155,7 +1191,7 @@ static su3_launch lookup_launch(int expr, int prec, int layout, int lanes,
     su3_launch c;
     return tuned_launch(expr, prec, layout, lanes, V, &c)
                ? c
-               : default_launch(expr, prec, layout, V);
+               : default_launch(expr, prec, layout, lanes, V);
 }
 
 // Workgroups of a walk that a CU holds.
@@ -1273,7 +1309,7 @@ static su3_launch plan_dslash(int prec, int layout, int64_t L, const int32_t dim
         o[mu] = dims[mu] / simd[mu];
         V *= dims[mu];
     }
-    su3_launch c = default_launch(SU3_EXPR_DSLASH, prec, layout, V);
+    su3_launch c = default_launch(SU3_EXPR_DSLASH, prec, layout, 0, V);
     // One wave per hop where the lattice cannot fill the chip otherwise (16^3
     // x 32, two-row links: 12.7 us, walks 46.8, one lane per site 15.8) and
     // as long as its second reads of each spinor come from the caches: to
@@ -2003,7 +2039,7 @@ static su3_launch program_launch(const su3_program *p, const su3_field *z,
                                  const su3_field *const *ops, int arith, const RowCode *rows,
                                  int form)
 {
-    su3_launch c = default_launch(SU3_EXPR_PROGRAM, arith, z->layout, z->V);
+    su3_launch c = default_launch(SU3_EXPR_PROGRAM, arith, z->layout, z->lanes, z->V);
     int64_t bytes = (int64_t)z->bytes;
     for (int k = 0; k < p->code.nops; ++k)
         if (p->code.used >> k & 1)
@@ -2235,7 +2271,7 @@ extern "C" su3_status su3_launch_get(su3_expr expr, su3_precision prec,
         return st;
     if (tuned_launch(expr, prec, layout, std::get<3>(k), s.V, out))
         return SU3_OK;
-    *out = default_launch(expr, prec, layout, s.V);
+    *out = default_launch(expr, prec, layout, std::get<3>(k), s.V);
     if (expr == SU3_EXPR_DSLASH) {
         int32_t simd[4] = {1, 1, 1, 1};
         if (layout == SU3_LAYOUT_VNODE)
@@ -2362,7 +2398,7 @@ static std::vector<su3_launch> candidates(int layout, int expr, int prec)
 static std::vector<su3_launch> dslash_candidates(int cbytes, int lx, int nsub)
 {
     std::vector<su3_launch> out;
-    su3_launch c = default_launch(SU3_EXPR_DSLASH, SU3_F64, SU3_LAYOUT_SOA, 0);
+    su3_launch c = default_launch(SU3_EXPR_DSLASH, SU3_F64, SU3_LAYOUT_SOA, 0, 0);
     c.nontemporal = 2;
     // virtual nodes: one site per lane in index order, or row tiles
     for (int walk : {1, 4, 8})
@@ -2427,7 +2463,7 @@ static std::vector<su3_launch> dslash_candidates(int cbytes, int lx, int nsub)
 static std::vector<su3_launch> program_candidates()
 {
     std::vector<su3_launch> out;
-    su3_launch c = default_launch(SU3_EXPR_PROGRAM, SU3_F64, SU3_LAYOUT_SOA, 0);
+    su3_launch c = default_launch(SU3_EXPR_PROGRAM, SU3_F64, SU3_LAYOUT_SOA, 0, 0);
     for (int b : {64, 128, 256})
         for (int occ : {0, 2, 3, 4, 6, 8})
             for (int nt : {0, 2, 3}) {
@@ -2541,7 +2577,7 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
         }
     }
     size_t turn = 0;
-    su3_launch win = default_launch(expr, prec, layout, s.V);
+    su3_launch win = default_launch(expr, prec, layout, std::get<3>(k), s.V);
     double win_us = 1e300;
     // expression programs are timed on the streaming product a*b, those
     // with a scalar result on the trace of a product
@@ -2565,7 +2601,7 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
             if (expr == SU3_EXPR_CSHIFT && c.schedule)
                 continue;  // a copy has no row phases
             if (program || expr == SU3_EXPR_CSHIFT || expr == SU3_EXPR_MUL_SHIFTED)
-                c.xcd_remap = default_launch(expr, prec, layout, f0->V).xcd_remap;
+                c.xcd_remap = default_launch(expr, prec, layout, f0->lanes, f0->V).xcd_remap;
             double us = 0;
             su3_status r = time_launch(
                 [&]() {
@@ -2740,7 +2776,8 @@ static su3_status plan_batch(const su3_expr *exprs, su3_field *const *z,
                 if (bytes[q] > bytes[prec])
                     prec = q;
         }
-        cfg = default_launch(SU3_EXPR_BATCH + exprs[0], prec, z[0]->layout, total_sites);
+        cfg = default_launch(SU3_EXPR_BATCH + exprs[0], prec, z[0]->layout, z[0]->lanes,
+                             total_sites);
     }
     const int T = cfg.tile_sites;
     // tile table: item i owns ceil(V_i / T) tiles starting at the exclusive
@@ -2995,7 +3032,7 @@ extern "C" su3_status su3_batch_autotune(const su3_expr *exprs,
     for (int i = 0; i < n; ++i)
         if (z[i])
             total += z[i]->V;
-    su3_launch win = default_launch(exprs[0], z[0]->prec, z[0]->layout, total);
+    su3_launch win = default_launch(exprs[0], z[0]->prec, z[0]->layout, z[0]->lanes, total);
     double win_us = 1e300;
     for (const su3_launch &c : batch_candidates()) {
         su3_batch *b = nullptr;
