@@ -2010,7 +2010,8 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
     const int64_t slots = (int64_t)pc.rows.nslots * kRowSlotVecs * spl * 2 * real_bytes(arith);
     // every workgroup resident at once: nothing to gain from smaller ones
     // (force term, six slots, FP64 12^4: 12.1 us, with registers 14.3)
-    if (groups <= f.cus * (f.lds_per_cu / slots))
+    const int64_t at_once = f.cus * (f.lds_per_cu / slots);
+    if (groups <= at_once)
         return &pc.rows;
     // Up to four slots of 9 KB the registers cost more than the waves they
     // make room for (FP64 48^4 a*b+c*d: 630 us, with registers 646); beyond,
@@ -2024,17 +2025,36 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
     // one-lane kernel, 48^4 trace(a*b*adj(c)*adj(d)) 283 against 259).
     if (pc.rows.nslots == 4 && arith == SU3_F32 && !aos)
         return nullptr;
+    // Three slots in single, 5 workgroups per CU, gain 4 to 10 % where they take
+    // no more rounds than the one-lane kernel with its 12 waves per CU, and lose
+    // more in calls of a few rounds where they take one more (c*a*b+0.5, 20^3 x
+    // 24, two rounds, 11.5 us against 8.7 in one; 25, two and two, 11.5 and 12.6;
+    // 24^4, three and two, 16.9 and 15.2).
+    const int64_t lane_groups = (z->V + 63) / 64, lanes_at_once = 12 * (int64_t)f.cus;
+    if (pc.rows.nslots == 3 && arith == SU3_F32 && !aos && groups < 3 * at_once &&
+        (groups + at_once - 1) / at_once > (lane_groups + lanes_at_once - 1) / lanes_at_once)
+        return nullptr;
     return &pc.rows;
 }
 
 // The launch of a program that nothing tuned or set (rows: its row form).
-// Loads stay cached in calls that the Infinity Cache holds with the fields in
-// use around them (FP32 24^4 a*adj(b), 72 MB: 12.9 us against 14.3; FP64
-// 48^3 x 24 a+b+a*b on real fields, 64 MB: 11.9 against 12.6),
-// where a lane-block's entry is less than a 128-byte line (FP32 AoSoA-8 32^4
-// a*b+c*d: 66.6 us against 72.9), and for AoS sites read entry by entry.  One
-// product alone streams best with 5 workgroups per CU (FP64 48^4 a*adj(b):
-// 361 us, uncapped 405); longer programs want them all.
+// Stores are nontemporal, loads too, except
+// - where a lane-block's entry is less than a 128-byte line (FP32 AoSoA-8 32^4
+//   a*b+c*d: 66.6 us against 72.9), and for AoS sites read entry by entry; below
+//   64 bytes stores stay cached too (FP32 N_sub 2 22^4 a*adj(b): 13.3 us, with
+//   nontemporal stores 35.4);
+// - by rows from 80 to 150 MB (FP64 22^4 a*adj(b), 101 MB, three sets of fields
+//   in turn: 17.4 us against 20.4).  Below, the loads of a call that is repeated
+//   on the same fields are faster past the L2s (FP64 16^4 a*b+c*d, 47 MB, 8.5
+//   us, cached 10.3), and as fast with sets in turn; above, the Infinity Cache
+//   no longer holds them (FP64 26^4 a*adj(b) 35.4 and 33.1).  The one-lane kernel
+//   never gains by it (FP32 20^4 a*b+c*d 10.1, cached 11.7);
+// - AoS records, and programs without a matrix value in double, to 150 MB (FP64
+//   48^3 x 24 a+b+a*b on real fields, 64 MB: 11.9 us against 12.6; in single
+//   48^4, 64 MB: 13.0 us, past the caches 10.4).
+// One product alone streams best with 5 workgroups per CU beyond 600 MB (FP64
+// 48^4 a*adj(b): 361 us, uncapped 405; 36^4 117 and 119; FP32 36^4, 363 MB, 59.7
+// and 57.4); longer programs want them all.
 static su3_launch program_launch(const su3_program *p, const su3_field *z,
                                  const su3_field *const *ops, int arith, const RowCode *rows,
                                  int form)
@@ -2046,10 +2066,13 @@ static su3_launch program_launch(const su3_program *p, const su3_field *z,
             bytes += (int64_t)ops[k]->bytes;
     const int64_t MB = 1000 * 1000;
     const bool aos = z->layout == SU3_LAYOUT_AOS;
-    const bool split = form == PF_MATRIX &&
-                       (aos ? !rows : z->L * 2 * (int64_t)real_bytes(arith) < 128);
-    c.nontemporal = bytes <= 150 * MB || split ? 2 : 3;
-    if (rows && rows->n == 1 && bytes > 256 * MB && !aos)
+    const int64_t run = z->L * 2 * (int64_t)real_bytes(arith);
+    const bool split = form == PF_MATRIX && (aos ? !rows : run < 128);
+    const bool resident = bytes <= 150 * MB &&
+                          (form != PF_MATRIX ? arith == SU3_F64
+                                             : aos || (rows && bytes > 80 * MB));
+    c.nontemporal = split && !aos && run < 64 ? 0 : resident || split ? 2 : 3;
+    if (rows && rows->n == 1 && bytes > 600 * MB && !aos)
         c.occupancy = 5;
     return c;
 }

@@ -139,6 +139,59 @@ static void programs()
 
 // Traces of negatives and conjugates: each term changes its sign before the
 // sum, so sums that cancel keep the zero's sign.
+// Which launch an untuned program takes: by rows where that needs no more
+// rounds of workgroups than one lane per site (3 slots in single: 15 workgroups
+// of 128 sites at once on the three emulated compute units, 18 of the one-lane
+// kernel's), and which loads of operand 0 bypass the caches.
+static void program_launches()
+{
+    struct Case { const char *text; int kinds[4]; int n; int prec; Lay l; int d[4]; bool rows, bypass; };
+    static const Lay soa = {SU3_LAYOUT_SOA, 0};
+    static const char *const update = "c*a*b+0.5";
+    static const Case cases[] = {
+        {update, {M, M, R}, 3, SU3_F32, soa, {8, 4, 4, 15}, true, true},   // 1 round, 1
+        {update, {M, M, R}, 3, SU3_F32, soa, {8, 4, 4, 16}, false, true},  // 2, 1
+        {update, {M, M, R}, 3, SU3_F32, soa, {8, 4, 4, 18}, false, true},  // 2, 1
+        {update, {M, M, R}, 3, SU3_F32, soa, {8, 4, 4, 19}, true, true},   // 2, 2
+        {update, {M, M, R}, 3, SU3_F32, soa, {8, 4, 4, 31}, false, true},  // 3, 2
+        {update, {M, M, R}, 3, SU3_F32, soa, {8, 4, 4, 37}, true, true},   // 3, 3
+        {update, {M, M, R}, 3, SU3_F64, soa, {8, 4, 4, 31}, true, true},
+        {"a*adj(b)", {M, M}, 2, SU3_F64, soa, {24, 24, 24, 13}, true, true},   // 78 MB
+        {"a*adj(b)", {M, M}, 2, SU3_F64, soa, {24, 24, 24, 14}, true, false},  // 84 MB
+        {"a*adj(b)", {M, M}, 2, SU3_F64, soa, {24, 24, 24, 26}, true, true},   // 155 MB
+        {"a*b+c*d", {M, M, M, M}, 4, SU3_F32, soa, {24, 24, 24, 18}, false, true},  // 90 MB
+        {"a*b+c*d", {M, M, M, M}, 4, SU3_F32, {SU3_LAYOUT_AOSOA, 8}, {8, 8, 8, 8}, false, false},
+        {"a*adj(b)", {M, M}, 2, SU3_F32, {SU3_LAYOUT_VNODE, 2}, {4, 4, 4, 4}, true, false},
+        {"a+b+a*b", {R, R}, 2, SU3_F32, soa, {8, 8, 8, 8}, false, true},
+        {"a+b+a*b", {R, R}, 2, SU3_F64, soa, {8, 8, 8, 8}, false, false}};
+    for (const Case &c : cases) {
+        su3_program *p;
+        su3_kind kinds[4], rk;
+        std::vector<su3_field *> f;
+        for (int k = 0; k < c.n; ++k) {
+            kinds[k] = (su3_kind)c.kinds[k];
+            f.push_back(make(c.d, c.prec, c.kinds[k], c.l, nullptr));
+        }
+        if (su3_program_create(&p, c.text, c.n, kinds) != SU3_OK) { CHECK(false, "%s: %s", c.text, su3_last_error()); continue; }
+        su3_program_info(p, &rk, nullptr, nullptr);
+        su3_field *z = make(c.d, c.prec, rk, c.l, nullptr);
+        void *q;
+        size_t n;
+        su3_field_data(f[0], &q, &n);
+        emu_watch_lo = (const char *)q;
+        emu_watch_hi = emu_watch_lo + n;
+        emu_watched = 0;
+        CHECK(su3_program_eval(p, z, f.data(), c.n, nullptr) == SU3_OK, "%s: %s", c.text, su3_last_error());
+        CHECK((blockDim.x == 192) == c.rows, "%s prec %d layout %d/%d t %d: %u lanes", c.text, c.prec, c.l.layout, c.l.lanes, c.d[3], blockDim.x);
+        CHECK((emu_watched > 0) == c.bypass, "%s prec %d layout %d/%d t %d: %ld loads bypass the caches", c.text, c.prec, c.l.layout, c.l.lanes, c.d[3], emu_watched);
+        emu_watch_lo = emu_watch_hi = nullptr;
+        for (su3_field *x : f) su3_field_free(x);
+        su3_field_free(z);
+        su3_program_destroy(p);
+    }
+    std::printf("program launches done\n");
+}
+
 static void traces()
 {
     static const char *const texts[] = {"trace(-a)", "trace(conj(a))", "trace(adj(-a))", "trace(transpose(-conj(a)))", "-trace(a)"};
@@ -360,6 +413,7 @@ static void staging()
 int main()
 {
     programs();
+    program_launches();
     traces();
     hopping();
     t_links();
