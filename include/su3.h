@@ -177,6 +177,8 @@ typedef struct su3_program su3_program;
  *               result entry; 1: row-phased -- right-hand operands in
  *               full, then per result row the left operands' row, the
  *               row's evaluation and its stores.
+ *               Programs: 0: the setting holds for every program of the
+ *               key; 1: for one form of them (su3_program_eval).
  *               su3_dslash (lexicographic layouts): with one site per
  *               lane, 0 takes sites in index order and 1..3 give each
  *               workgroup a 4D tile of sites, 8x4x2x(B/64), 4x4x4x(B/64),
@@ -432,8 +434,11 @@ su3_status su3_program_info(const su3_program *p, su3_kind *result_kind,
  * (workgroups of three waves ignore its block), that of
  * SU3_EXPR_PROGRAM_SCALAR to programs with matrix values and a real or complex
  * result; a call without one takes cached or streaming loads, its occupancy
- * cap and XCD ranges by its bytes and layout.  Programs without a matrix value take only its
- * nontemporal bits and run 256-lane workgroups with no occupancy cap. */
+ * cap and XCD ranges by its bytes and layout.  A setting of schedule 0 holds for
+ * every program of the key, one of schedule 1 (the tuner's) for those that run
+ * as the key's own program does: a*b, trace(a*adj(b)).  Programs without a matrix
+ * value take only the nontemporal bits of SU3_EXPR_PROGRAM's setting of schedule
+ * 0 and run 256-lane workgroups with no occupancy cap. */
 su3_status su3_program_eval(const su3_program *p, su3_field *z,
                             const su3_field *const *ops, int32_t n_ops,
                             void *stream);
@@ -536,7 +541,11 @@ su3_status su3_batch_tiles(const su3_batch *b, int32_t *rows, int64_t cap,
  * are allocated and freed internally; when one set of operands takes 64
  * to 512 MiB, enough sets for 1 GiB are allocated and launched in
  * rotation, so the launch is tuned for operands that are not in the
- * Infinity Cache.  `best` may be NULL. */
+ * Infinity Cache.  Programs are timed in the form of the key's own program;
+ * in SU3_F32, on layouts other than AoS, also on one lane per site, with four
+ * operands (a*b+c*d, trace(a*b*adj(c)*adj(d))), if there is room for those:
+ * that setting is kept and saved beside the first, which `best` and
+ * su3_launch_get return.  su3_launch_set replaces both.  `best` may be NULL. */
 su3_status su3_autotune(su3_expr expr, su3_precision prec, su3_layout layout,
                         int32_t lanes, const int32_t dims[4], void *stream,
                         su3_launch *best);

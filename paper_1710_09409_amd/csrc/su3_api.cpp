@@ -1185,6 +1185,37 @@ static bool tuned_launch(int expr, int prec, int layout, int lanes, int64_t V,
     return true;
 }
 
+// Program keys hold two settings: that of the form of their own program (a*b,
+// trace(a*adj(b)): by rows, the trace on AoS fields on one lane per site), and,
+// under kOtherForm, that of the other form.
+static const int kOtherForm = 1 << 16;
+
+static bool is_program_key(int expr)
+{
+    return expr == SU3_EXPR_PROGRAM || expr == SU3_EXPR_PROGRAM_SCALAR;
+}
+
+// The setting of a program's key (form: PF_*, by_rows) that holds for it.  A
+// setting of schedule 0 holds for every program of the key, as a caller sets it;
+// the tuner's, of schedule 1, for the form it was timed on: the caps that suit
+// one form cost the other up to half (FP32 48^4 a*b+c*d on one lane per site,
+// with the cap that is best for a*b by rows 481 us, with its own 318).
+// Nor does the cap that suits one product suit longer programs by rows (FP64 48^4
+// c*a*b+0.5: with a*b's 399 us, uncapped 368).
+static bool tuned_program(int expr, int prec, const su3_field *z, int form, const RowCode *rows,
+                          su3_launch *c)
+{
+    const bool own = !rows == (expr == SU3_EXPR_PROGRAM_SCALAR && z->layout == SU3_LAYOUT_AOS);
+    if (tuned_launch(expr, prec, z->layout, z->lanes, z->V, c) &&
+        (c->schedule == 0 || (form == PF_MATRIX && own))) {
+        if (c->schedule == 1 && rows && rows->n > 1)
+            c->occupancy = 0;
+        return true;
+    }
+    return form == PF_MATRIX && !own &&
+           tuned_launch(expr + kOtherForm, prec, z->layout, z->lanes, z->V, c);
+}
+
 static su3_launch lookup_launch(int expr, int prec, int layout, int lanes,
                                 int64_t V)
 {
@@ -1462,6 +1493,14 @@ static void load_cache_locked()
             c.sites_per_lane = 0;
         if (check_launch(c, la, ex) != SU3_OK)
             continue;
+        if (is_program_key(ex)) {
+            // lines that name no form are from before there were two
+            if (c.schedule == 0)
+                continue;
+            int other = 0;
+            (void)parse_int(line, "other_form", &other);
+            ex += other ? kOtherForm : 0;
+        }
         g_tuned[Key(ex, pr, la, ln, vb)] = c;
     }
     fclose(fp);
@@ -1480,11 +1519,12 @@ static void append_cache(const Key &k, const su3_launch &c, double us)
             "\"lanes\":%d,\"vbucket\":%d,\"block\":%d,\"persistent\":%d,"
             "\"nontemporal\":%d,\"xcd_remap\":%d,\"lds_stage\":%d,"
             "\"tile_sites\":%d,\"occupancy\":%d,\"schedule\":%d,"
-            "\"sites_per_lane\":%d,\"us\":%.3f}\n",
-            device_tag().c_str(), std::get<0>(k), std::get<1>(k),
+            "\"sites_per_lane\":%d,%s\"us\":%.3f}\n",
+            device_tag().c_str(), std::get<0>(k) & ~kOtherForm, std::get<1>(k),
             std::get<2>(k), std::get<3>(k), std::get<4>(k), c.block,
             c.persistent, c.nontemporal, c.xcd_remap, c.lds_stage,
-            c.tile_sites, c.occupancy, c.schedule, c.sites_per_lane, us);
+            c.tile_sites, c.occupancy, c.schedule, c.sites_per_lane,
+            std::get<0>(k) & kOtherForm ? "\"other_form\":1," : "", us);
     fclose(fp);
 }
 
@@ -2094,7 +2134,7 @@ static su3_status launch_program_op(const su3_program *p, su3_field *z,
     su3_launch c;
     if (forced)
         c = *forced;
-    else if (!tuned_launch(key, arith, z->layout, z->lanes, z->V, &c))
+    else if (!tuned_program(key, arith, z, form, rows, &c))
         c = program_launch(p, z, ops, arith, rows, form);
     if (!forced && form != PF_MATRIX) {
         // the block and occupancy cap are the matrix kernel's (a wave of it
@@ -2324,6 +2364,8 @@ extern "C" su3_status su3_launch_set(su3_expr expr, su3_precision prec,
     std::lock_guard<std::mutex> lk(g_tune_mu);
     load_cache_locked();
     g_tuned[k] = *cfg;
+    std::get<0>(k) += kOtherForm;
+    g_tuned.erase(k);
     return SU3_OK;
 }
 
@@ -2481,15 +2523,17 @@ static std::vector<su3_launch> dslash_candidates(int cbytes, int lx, int nsub)
     return out;
 }
 
-// Candidates for the program kernel: one site per lane, one-shot grid;
-// block, occupancy cap, nontemporal bits.
-static std::vector<su3_launch> program_candidates()
+// Candidates for a program: occupancy cap and nontemporal bits, and on one
+// lane per site the block (workgroups by rows are three waves).
+static std::vector<su3_launch> program_candidates(bool by_rows)
 {
     std::vector<su3_launch> out;
     su3_launch c = default_launch(SU3_EXPR_PROGRAM, SU3_F64, SU3_LAYOUT_SOA, 0, 0);
     for (int b : {64, 128, 256})
-        for (int occ : {0, 2, 3, 4, 6, 8})
+        for (int occ : {0, 2, 3, 4, 5, 6, 8})
             for (int nt : {0, 2, 3}) {
+                if (by_rows && b != 128)
+                    continue;
                 c.block = b;
                 c.occupancy = occ;
                 c.nontemporal = nt;
@@ -2603,24 +2647,23 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
     su3_launch win = default_launch(expr, prec, layout, std::get<3>(k), s.V);
     double win_us = 1e300;
     // expression programs are timed on the streaming product a*b, those
-    // with a scalar result on the trace of a product
-    const bool program = expr == SU3_EXPR_PROGRAM || expr == SU3_EXPR_PROGRAM_SCALAR;
-    su3_program prog;
-    if (st == SU3_OK && program) {
-        const int kinds[2] = {KIND_MATRIX, KIND_MATRIX};
-        char err[128];
-        const char *text = expr == SU3_EXPR_PROGRAM ? "a*b" : "trace(a*adj(b))";
-        if (!compile_program(text, 2, kinds, &prog.code, err, sizeof err))
-            st = fail(SU3_ERR_HIP, "internal program: %s", err);
-    }
-    if (st == SU3_OK) {
+    // with a scalar result on the trace of a product; in single, where programs
+    // of four operands run on one lane per site, these too
+    const bool program = is_program_key(expr), traced = expr == SU3_EXPR_PROGRAM_SCALAR;
+    const bool other_form = program && prec == SU3_F32 && layout != SU3_LAYOUT_AOS;
+    su3_program prog, prog4;
+    const int kinds[4] = {KIND_MATRIX, KIND_MATRIX, KIND_MATRIX, KIND_MATRIX};
+    char err[128];
+    if (st == SU3_OK && program &&
+        (!compile_program(traced ? "trace(a*adj(b))" : "a*b", 2, kinds, &prog.code, err,
+                          sizeof err) ||
+         !compile_program(traced ? "trace(a*b*adj(c)*adj(d))" : "a*b+c*d", 4, kinds,
+                          &prog4.code, err, sizeof err)))
+        st = fail(SU3_ERR_HIP, "internal program: %s", err);
+    const auto sweep = [&](const std::vector<su3_launch> &list, const su3_program *pr,
+                           su3_launch *win, double *win_us) {
         const su3_field *f0 = sets[0][0];
-        for (su3_launch c : dslash ? dslash_candidates(2 * f0->rbytes,
-                                                              f0->dims[0] / f0->simd[0],
-                                                              layout == SU3_LAYOUT_VNODE
-                                                                  ? (int)f0->L : 1)
-                                   : program ? program_candidates()
-                                                              : candidates(layout, expr, prec)) {
+        for (su3_launch c : list) {
             if (expr == SU3_EXPR_CSHIFT && c.schedule)
                 continue;  // a copy has no row phases
             if (program || expr == SU3_EXPR_CSHIFT || expr == SU3_EXPR_MUL_SHIFTED)
@@ -2634,7 +2677,7 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
                     if (dslash)
                         return launch_dslash_op(f[0], links, f[1], stream, &c);
                     if (program)
-                        return launch_program_op(&prog, f[0], ops, prec, hs, &c);
+                        return launch_program_op(pr, f[0], ops, prec, hs, &c);
                     if (expr == SU3_EXPR_CSHIFT)
                         return launch_shift_op(0, f[0], nullptr, f[1], 1, 1,
                                                stream, &c);
@@ -2648,25 +2691,72 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
                 (void)hipGetLastError();
                 continue;  // a launch shape the device refused
             }
-            if (us < win_us) {
-                win_us = us;
-                win = c;
+            if (us < *win_us) {
+                *win_us = us;
+                *win = c;
             }
         }
+    };
+    // the candidates of a program, its untuned launch first
+    const auto program_list = [&](const su3_program *pr) {
+        su3_field *const *f = sets[0].data();
+        const su3_field *ops[4] = {f[1], f[2], f[3], f[4]};
+        const RowCode *rows = row_code(pr, f[0], prec);
+        std::vector<su3_launch> list = program_candidates(rows != nullptr);
+        list.insert(list.begin(), program_launch(pr, f[0], ops, prec, rows, PF_MATRIX));
+        for (su3_launch &c : list)
+            c.schedule = 1;  // for its form only
+        return list;
+    };
+    if (st == SU3_OK) {
+        const su3_field *f0 = sets[0][0];
+        sweep(dslash ? dslash_candidates(2 * f0->rbytes, f0->dims[0] / f0->simd[0],
+                                         layout == SU3_LAYOUT_VNODE ? (int)f0->L : 1)
+              : program ? program_list(&prog)
+                        : candidates(layout, expr, prec),
+              &prog, &win, &win_us);
         if (win_us >= 1e300)
             st = fail(SU3_ERR_HIP, "no candidate launch ran");
+    }
+    // the other form needs two operands more; without room for them it keeps
+    // its untuned launch
+    su3_launch win4 = win;
+    double win4_us = 1e300;
+    if (st == SU3_OK && other_form) {
+        bool room = true;
+        for (auto &set : sets)
+            for (int i = 3; i <= 4 && room; ++i) {
+                room = (layout == SU3_LAYOUT_VNODE
+                            ? alloc_of_kind(&set[i], dims, prec, layout, 0, KIND_MATRIX, simd)
+                            : alloc_of_kind(&set[i], dims, prec, layout, lanes, KIND_MATRIX)) ==
+                           SU3_OK &&
+                       hipMemsetD32Async((hipDeviceptr_t)set[i]->ptr, 0x3c003c00u,
+                                         set[i]->bytes / 4, hs) == hipSuccess;
+            }
+        if (room && row_code(&prog4, sets[0][0], prec) == nullptr)
+            sweep(program_list(&prog4), &prog4, &win4, &win4_us);
+        else
+            (void)hipGetLastError();
     }
     for (auto &set : sets)
         for (su3_field *fi : set)
             su3_field_free(fi);
     if (st != SU3_OK)
         return st;
+    Key k4 = k;
+    std::get<0>(k4) += kOtherForm;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         load_cache_locked();
         g_tuned[k] = win;
+        if (win4_us < 1e300)
+            g_tuned[k4] = win4;
+        else if (program)
+            g_tuned.erase(k4);
     }
     append_cache(k, win, win_us);
+    if (win4_us < 1e300)
+        append_cache(k4, win4, win4_us);
     if (best)
         *best = win;
     if (best_us)

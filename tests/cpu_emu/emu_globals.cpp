@@ -17,6 +17,7 @@ int emu_atomics = 0, emu_failing_mallocs = 0, emu_frees = 0;
 std::vector<emu_call> emu_calls;
 const char *emu_watch_lo = nullptr, *emu_watch_hi = nullptr;
 long emu_watched = 0;
+float (*emu_launch_ms)() = nullptr;
 namespace su3k { namespace p0 { alignas(16) unsigned char lds[1 << 18]; } namespace p1 { alignas(16) unsigned char lds[1 << 18]; } namespace p2 { alignas(16) unsigned char lds[1 << 18]; } namespace p3 { alignas(16) unsigned char lds[1 << 18]; } }
 namespace su3k { char occupancy_reserve[1 << 16]; namespace p0 { char occupancy_reserve[1 << 16]; } namespace p1 { char occupancy_reserve[1 << 16]; } namespace p2 { char occupancy_reserve[1 << 16]; } namespace p3 { char occupancy_reserve[1 << 16]; } namespace dslash { alignas(16) char occupancy_reserve[160 << 10]; } namespace prog { alignas(16) char occupancy_reserve[160 << 10]; } }
 

@@ -5,7 +5,10 @@
 #include "su3.h"
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <fstream>
+#include <sstream>
 #include <string>
 #include <vector>
 #include <hip/hip_runtime.h>
@@ -190,6 +193,108 @@ static void program_launches()
         su3_program_destroy(p);
     }
     std::printf("program launches done\n");
+}
+
+// Settings of a program key: one that a caller sets holds for every program of
+// the key, the tuner's (schedule 1) for the form it was timed on; saved settings
+// that name no form are left out.
+static void program_settings()
+{
+    const int d[4] = {8, 4, 4, 16};  // 16 workgroups of 128 sites, 12 of four slots at once
+    const Lay l = {SU3_LAYOUT_SOA, 0};
+    const auto get = [&](su3_expr e, su3_precision prec) {
+        su3_launch c;
+        std::memset(&c, 0, sizeof c);
+        CHECK(su3_launch_get(e, prec, SU3_LAYOUT_SOA, 0, d, &c) == SU3_OK, "get: %s", su3_last_error());
+        return c;
+    };
+    const auto line = [&](int expr, int prec, int block, int schedule, const char *more) {
+        std::ostringstream o;
+        o << "{\"device\":\"emu:3\",\"expr\":" << expr << ",\"prec\":" << prec << ",\"layout\":1,\"lanes\":0,\"vbucket\":11,\"block\":" << block
+          << ",\"persistent\":0,\"nontemporal\":3,\"xcd_remap\":0,\"lds_stage\":0,\"tile_sites\":4096,\"occupancy\":0,\"schedule\":" << schedule
+          << ",\"sites_per_lane\":0," << more << "\"us\":1.0}\n";
+        return o.str();
+    };
+    char path[] = "/tmp/su3_forms_XXXXXX";
+    const int fd = mkstemp(path);
+    CHECK(fd >= 0, "mkstemp");
+    std::ofstream(path) << line(SU3_EXPR_PROGRAM, SU3_F64, 256, 0, "") << line(SU3_EXPR_PROGRAM_SCALAR, SU3_F32, 256, 1, "\"other_form\":1,")
+                        << line(SU3_EXPR_PROGRAM, SU3_F32, 64, 1, "");
+    setenv("SU3_TUNE_CACHE", path, 1);
+    CHECK(get(SU3_EXPR_PROGRAM, SU3_F64).block == 128, "a line without a form holds");
+    CHECK(get(SU3_EXPR_PROGRAM_SCALAR, SU3_F32).block == 128, "the other form's line holds for the first");
+    CHECK(get(SU3_EXPR_PROGRAM, SU3_F32).block == 64, "a line is lost");
+
+    // the programs: by rows, on one lane per site, without a matrix
+    struct Ex { const char *text; int n, kind; su3_program *p; su3_field *f[4], *z; };
+    Ex ex[] = {{"a*b", 2, M, nullptr, {}, nullptr}, {"a*b+c*d", 4, M, nullptr, {}, nullptr}, {"a+b", 2, R, nullptr, {}, nullptr},
+               {"trace(a*b*adj(c)*adj(d))", 4, M, nullptr, {}, nullptr}};
+    for (Ex &e : ex) {
+        su3_kind kinds[4], rk;
+        for (int k = 0; k < e.n; ++k) {
+            kinds[k] = (su3_kind)e.kind;
+            const std::vector<double> h = host_values(volume(d), e.kind, k);
+            e.f[k] = make(d, SU3_F32, e.kind, l, h.data());
+        }
+        CHECK(su3_program_create(&e.p, e.text, e.n, kinds) == SU3_OK, "%s: %s", e.text, su3_last_error());
+        su3_program_info(e.p, &rk, nullptr, nullptr);
+        e.z = make(d, SU3_F32, rk, l, nullptr);
+    }
+    // loads past the caches?  And the lanes of the launch
+    const auto run = [&](const Ex &e, unsigned *lanes) {
+        void *q;
+        size_t n;
+        su3_field_data(e.f[0], &q, &n);
+        emu_watch_lo = (const char *)q;
+        emu_watch_hi = emu_watch_lo + n;
+        emu_watched = 0;
+        CHECK(su3_program_eval(e.p, e.z, e.f, e.n, nullptr) == SU3_OK, "%s: %s", e.text, su3_last_error());
+        emu_watch_lo = emu_watch_hi = nullptr;
+        *lanes = blockDim.x;
+        return emu_watched > 0;
+    };
+    unsigned lanes;
+    CHECK(!(run(ex[3], &lanes), lanes != 256), "the trace on one lane per site: %u lanes, not as saved", lanes);
+    su3_launch_reset();
+    for (int schedule = 0; schedule < 2; ++schedule) {
+        su3_launch c = {64, 0, 0, 0, 0, 4096, 0, schedule, 0};
+        CHECK(su3_launch_set(SU3_EXPR_PROGRAM, SU3_F32, SU3_LAYOUT_SOA, 0, d, &c) == SU3_OK, "set: %s", su3_last_error());
+        const su3_launch g = get(SU3_EXPR_PROGRAM, SU3_F32);
+        CHECK(std::memcmp(&g, &c, sizeof c) == 0, "another setting than was set");
+        CHECK(!run(ex[0], &lanes) && lanes == 192, "schedule %d: not for a*b", schedule);
+        CHECK(run(ex[1], &lanes) == (schedule == 1) && lanes == (schedule ? 128u : 64u), "schedule %d: a*b+c*d in %u lanes", schedule, lanes);
+        CHECK(run(ex[2], &lanes) == (schedule == 1), "schedule %d: a+b", schedule);
+    }
+    // tuned where blocks of 256 lanes are fastest: the four operands' programs
+    // run in those, a*b by rows as untuned (all launches by rows took alike)
+    su3_launch_reset();
+    emu_launch_ms = [] { return blockDim.x == 256 ? 0.5f : 1.0f; };
+    for (su3_expr e : {SU3_EXPR_PROGRAM, SU3_EXPR_PROGRAM_SCALAR}) {
+        su3_launch best, was = get(e, SU3_F32);
+        CHECK(su3_autotune(e, SU3_F32, SU3_LAYOUT_SOA, 0, d, nullptr, &best) == SU3_OK, "autotune: %s", su3_last_error());
+        CHECK(best.schedule == 1, "the tuner's setting names no form");
+        was.schedule = 1;
+        CHECK(std::memcmp(&was, &best, sizeof was) == 0, "by rows: nontemporal %d, cap %d", best.nontemporal, best.occupancy);
+        const su3_launch g = get(e, SU3_F32);
+        CHECK(std::memcmp(&g, &best, sizeof g) == 0, "another setting than the tuner's");
+    }
+    emu_launch_ms = nullptr;
+    CHECK((run(ex[1], &lanes), lanes == 256), "a*b+c*d tuned: %u lanes", lanes);
+    CHECK((run(ex[3], &lanes), lanes == 256), "trace tuned: %u lanes", lanes);
+    std::stringstream saved;
+    saved << std::ifstream(path).rdbuf();
+    size_t others = 0;
+    for (size_t at = 0; (at = saved.str().find("\"other_form\":1", at)) != std::string::npos; ++at) ++others;
+    CHECK(others == 3, "%zu lines of the other form", others);
+    su3_launch_reset();
+    unsetenv("SU3_TUNE_CACHE");
+    std::remove(path);
+    for (Ex &e : ex) {
+        for (su3_field *f : e.f) su3_field_free(f);
+        su3_field_free(e.z);
+        su3_program_destroy(e.p);
+    }
+    std::printf("program settings done\n");
 }
 
 static void traces()
@@ -412,6 +517,7 @@ static void staging()
 
 int main()
 {
+    program_settings();
     programs();
     program_launches();
     traces();

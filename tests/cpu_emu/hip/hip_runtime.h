@@ -158,7 +158,8 @@ inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { emu_calls.push_b
 inline hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { emu_calls.push_back({'W', s, e}); return hipSuccess; }
 enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
 inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *c) { *c = emu_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
-inline hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
+extern float (*emu_launch_ms)();  // what the launch that ran last took (null: 1 ms)
+inline hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = emu_launch_ms ? emu_launch_ms() : 1.0f; return hipSuccess; }
 inline hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 inline hipError_t hipStreamCreateWithFlags(hipStream_t *s, int) { *s = (void *)1; return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
