@@ -542,9 +542,9 @@ su3_status su3_batch_tiles(const su3_batch *b, int32_t *rows, int64_t cap,
  * to 512 MiB, enough sets for 1 GiB are allocated and launched in
  * rotation, so the launch is tuned for operands that are not in the
  * Infinity Cache.  Programs are timed in the form of the key's own program;
- * in SU3_F32, on layouts other than AoS, also on one lane per site, with four
- * operands (a*b+c*d, trace(a*b*adj(c)*adj(d))), if there is room for those:
- * that setting is kept and saved beside the first, which `best` and
+ * where that is by rows and programs of four operands run on one lane per
+ * site, also a*b+c*d or trace(a*b*adj(c)*adj(d)), if there is room for it: that
+ * setting is kept and saved beside the first, which `best` and
  * su3_launch_get return.  su3_launch_set replaces both.  `best` may be NULL. */
 su3_status su3_autotune(su3_expr expr, su3_precision prec, su3_layout layout,
                         int32_t lanes, const int32_t dims[4], void *stream,

@@ -1186,13 +1186,26 @@ static bool tuned_launch(int expr, int prec, int layout, int lanes, int64_t V,
 }
 
 // Program keys hold two settings: that of the form of their own program (a*b,
-// trace(a*adj(b)): by rows, the trace on AoS fields on one lane per site), and,
-// under kOtherForm, that of the other form.
+// trace(a*adj(b)): by rows, on AoS fields the trace and large products on one lane
+// per site), and, under kOtherForm, that of the other form.
 static const int kOtherForm = 1 << 16;
 
 static bool is_program_key(int expr)
 {
     return expr == SU3_EXPR_PROGRAM || expr == SU3_EXPR_PROGRAM_SCALAR;
+}
+
+// AoS matrices up to which one product runs by rows, and their bytes.
+static const int64_t kAosRowBytes = (int64_t)50 * 1000 * 1000;
+
+static int64_t aos_bytes(const su3_field *z, int arith)
+{
+    return z->V * 18 * real_bytes(arith);
+}
+
+static bool row_product_aos(const su3_field *z, int arith)
+{
+    return aos_bytes(z, arith) <= kAosRowBytes;
 }
 
 // The setting of a program's key (form: PF_*, by_rows) that holds for it.  A
@@ -1205,7 +1218,9 @@ static bool is_program_key(int expr)
 static bool tuned_program(int expr, int prec, const su3_field *z, int form, const RowCode *rows,
                           su3_launch *c)
 {
-    const bool own = !rows == (expr == SU3_EXPR_PROGRAM_SCALAR && z->layout == SU3_LAYOUT_AOS);
+    const bool own_rows = z->layout != SU3_LAYOUT_AOS ||
+                          (expr == SU3_EXPR_PROGRAM && row_product_aos(z, prec));
+    const bool own = (rows != nullptr) == own_rows;
     if (tuned_launch(expr, prec, z->layout, z->lanes, z->V, c) &&
         (c->schedule == 0 || (form == PF_MATRIX && own))) {
         if (c->schedule == 1 && rows && rows->n > 1)
@@ -2040,17 +2055,33 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
         return nullptr;
     // AoS matrices without a matrix to store: the one-lane kernel's cached
     // loads reach the rest of a site's record in the same lines (FP64 32^4
-    // trace(a*adj(b)): 58 us against 88 through LDS); with one, its stores of
-    // 16 bytes per record cost more (a*adj(b): 368 us against 101).
+    // trace(a*adj(b)): 58 us against 88 through LDS).
     if (aos && pc.result_kind != FK_MATRIX)
         return nullptr;
     const DeviceFacts f = device_facts(z->device);
     const int spl = row_sites_per_lane(z, arith);
     const int64_t groups = (z->V + 64 * spl - 1) / (64 * spl);
     const int64_t slots = (int64_t)pc.rows.nslots * kRowSlotVecs * spl * 2 * real_bytes(arith);
+    const int64_t at_once = f.cus * (f.lds_per_cu / slots);
+    // AoS with a matrix to store: the one-lane kernel's cached stores reach the
+    // rest of the record likewise.  By rows go a product of fields in the caches
+    // (FP64 16^4 a*adj(b) 6.5 us against 8.0, 24^4 28.3 both, 48^4 494 against 450;
+    // FP32 24^4 20.1 and 23.0, 32^4 in turn 71 and 68), programs of three slots, in
+    // double of smaller ones (c*a*b+0.5 in turn 22^4 27.3 and 30.3, 24^4 50 and 40;
+    // FP32 28^4 44.7 and 48.3), and of more than four in one round (force term
+    // FP32 16^4 13.3 and 16.8, FP64 16^4, two rounds, 32.8 and 25.1; four slots,
+    // FP64 a*b+c*d, 12^4 8.2 and 7.1, 48^4 1391 and 731).
+    if (aos) {
+        const bool cached = row_product_aos(z, arith);
+        const bool small = arith == SU3_F32 || 10 * aos_bytes(z, arith) <= 7 * kAosRowBytes;
+        return (pc.rows.nslots <= 2   ? cached
+                : pc.rows.nslots == 3 ? cached && small
+                                      : pc.rows.nslots > 4 && groups <= at_once)
+                   ? &pc.rows
+                   : nullptr;
+    }
     // every workgroup resident at once: nothing to gain from smaller ones
     // (force term, six slots, FP64 12^4: 12.1 us, with registers 14.3)
-    const int64_t at_once = f.cus * (f.lds_per_cu / slots);
     if (groups <= at_once)
         return &pc.rows;
     // Up to four slots of 9 KB the registers cost more than the waves they
@@ -2059,11 +2090,11 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
     // us in slots, 1090 with registers, 1437 on the one-lane kernel; FP32 855,
     // 517 and 560).
     if (pc.rows.nslots > 4)
-        return aos ? &pc.rows_aos : &pc.rows_held;
+        return &pc.rows_held;
     // Four slots: 12 waves per CU with the loads of 16 bytes per lane and row
     // are too few in single (FP32 20^4 a*b+c*d: 14.7 us against 11.5 on the
     // one-lane kernel, 48^4 trace(a*b*adj(c)*adj(d)) 283 against 259).
-    if (pc.rows.nslots == 4 && arith == SU3_F32 && !aos)
+    if (pc.rows.nslots == 4 && arith == SU3_F32)
         return nullptr;
     // Three slots in single, 5 workgroups per CU, gain 4 to 10 % where they take
     // no more rounds than the one-lane kernel with its 12 waves per CU, and lose
@@ -2071,7 +2102,7 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
     // 24, two rounds, 11.5 us against 8.7 in one; 25, two and two, 11.5 and 12.6;
     // 24^4, three and two, 16.9 and 15.2).
     const int64_t lane_groups = (z->V + 63) / 64, lanes_at_once = 12 * (int64_t)f.cus;
-    if (pc.rows.nslots == 3 && arith == SU3_F32 && !aos && groups < 3 * at_once &&
+    if (pc.rows.nslots == 3 && arith == SU3_F32 && groups < 3 * at_once &&
         (groups + at_once - 1) / at_once > (lane_groups + lanes_at_once - 1) / lanes_at_once)
         return nullptr;
     return &pc.rows;
@@ -2089,9 +2120,10 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
 //   us, cached 10.3), and as fast with sets in turn; above, the Infinity Cache
 //   no longer holds them (FP64 26^4 a*adj(b) 35.4 and 33.1).  The one-lane kernel
 //   never gains by it (FP32 20^4 a*b+c*d 10.1, cached 11.7);
-// - AoS records, and programs without a matrix value in double, to 150 MB (FP64
-//   48^3 x 24 a+b+a*b on real fields, 64 MB: 11.9 us against 12.6; in single
-//   48^4, 64 MB: 13.0 us, past the caches 10.4).
+// - AoS records, and programs without a matrix value, to 150 MB (FP64 48^3 x 24
+//   a+b+a*b on real fields, 64 MB: 11.9 us against 12.6; FP32 36^4 a*conj(b)+a on
+//   AoS complex ones 9.6 and 12.4; but in single 48^4 real ones, 64 MB: 13.0 us,
+//   past the caches 10.4).
 // One product alone streams best with 5 workgroups per CU beyond 600 MB (FP64
 // 48^4 a*adj(b): 361 us, uncapped 405; 36^4 117 and 119; FP32 36^4, 363 MB, 59.7
 // and 57.4); longer programs want them all.
@@ -2109,9 +2141,18 @@ static su3_launch program_launch(const su3_program *p, const su3_field *z,
     const int64_t run = z->L * 2 * (int64_t)real_bytes(arith);
     const bool split = form == PF_MATRIX && (aos ? !rows : run < 128);
     const bool resident = bytes <= 150 * MB &&
-                          (form != PF_MATRIX ? arith == SU3_F64
+                          (form != PF_MATRIX ? form == PF_SCALAR || arith == SU3_F64
                                              : aos || (rows && bytes > 80 * MB));
     c.nontemporal = split && !aos && run < 64 ? 0 : resident || split ? 2 : 3;
+    if (aos && split && p->code.result_kind == FK_MATRIX) {
+        // stores cached too (FP64 32^4 a*adj(b) 108 us, nontemporal 439); few
+        // waves, whose records stay in the caches until they are done (93 us with
+        // 4 per CU, and no program slower; FP32 48^4 a*b+c*d 442 with 8, uncapped
+        // 501, but 24^4 32.5 and 29.9)
+        c.nontemporal = 0;
+        c.block = 64;
+        c.occupancy = arith == SU3_F64 ? 4 : aos_bytes(z, arith) > kAosRowBytes ? 8 : 0;
+    }
     if (rows && rows->n == 1 && bytes > 600 * MB && !aos)
         c.occupancy = 5;
     return c;
@@ -2647,10 +2688,9 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
     su3_launch win = default_launch(expr, prec, layout, std::get<3>(k), s.V);
     double win_us = 1e300;
     // expression programs are timed on the streaming product a*b, those
-    // with a scalar result on the trace of a product; in single, where programs
-    // of four operands run on one lane per site, these too
+    // with a scalar result on the trace of a product; where programs of four
+    // operands run in the other form, on one lane per site, these too
     const bool program = is_program_key(expr), traced = expr == SU3_EXPR_PROGRAM_SCALAR;
-    const bool other_form = program && prec == SU3_F32 && layout != SU3_LAYOUT_AOS;
     su3_program prog, prog4;
     const int kinds[4] = {KIND_MATRIX, KIND_MATRIX, KIND_MATRIX, KIND_MATRIX};
     char err[128];
@@ -2722,7 +2762,8 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
     // its untuned launch
     su3_launch win4 = win;
     double win4_us = 1e300;
-    if (st == SU3_OK && other_form) {
+    if (st == SU3_OK && program && row_code(&prog, sets[0][0], prec) &&
+        !row_code(&prog4, sets[0][0], prec)) {
         bool room = true;
         for (auto &set : sets)
             for (int i = 3; i <= 4 && room; ++i) {
@@ -2733,7 +2774,7 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
                        hipMemsetD32Async((hipDeviceptr_t)set[i]->ptr, 0x3c003c00u,
                                          set[i]->bytes / 4, hs) == hipSuccess;
             }
-        if (room && row_code(&prog4, sets[0][0], prec) == nullptr)
+        if (room)
             sweep(program_list(&prog4), &prog4, &win4, &win4_us);
         else
             (void)hipGetLastError();

@@ -1454,8 +1454,7 @@ static hipError_t pick_rows(int nt, size_t shm, const su3i::RowArgs &a, hipStrea
 {
     if constexpr (S == 1) {
         if (a.aos)
-            return a.held ? go_rows<T, 1, ROWF_AOS | ROWF_HELD>(nt, shm, a, st)
-                          : go_rows<T, 1, ROWF_AOS>(nt, shm, a, st);
+            return a.held ? hipErrorInvalidValue : go_rows<T, 1, ROWF_AOS>(nt, shm, a, st);
     }
     return a.held ? go_rows<T, S, ROWF_HELD>(nt, shm, a, st) : go_rows<T, S, 0>(nt, shm, a, st);
 }

@@ -472,10 +472,8 @@ struct RowGen {
         return i.op == ROW_TRACE || (matrix_a(i.op) && (i.am & ROW_TRANS));
     }
 
-    enum Registers { NO_REGISTERS, HOLD_RESULTS, HOLD_ALL };
-
-    // Slots, registers and barriers; false when it does not fit.
-    bool lower(Val res, unsigned used, Registers regs, RowCode *out)
+    // Slots, registers (if asked for) and barriers; false when it does not fit.
+    bool lower(Val res, unsigned used, bool registers, RowCode *out)
     {
         if (res.src != nops + (int)ins.size() - 1 || res.mode != 0 || ins.empty())
             ins.push_back({res.ty == T_MATRIX ? ROW_MOV_M : ROW_MOV_S, res.src, res.mode, res.src,
@@ -515,7 +513,7 @@ struct RowGen {
         std::fill(held, held + kRowRegisters, -1);
         const auto hold = [&](int v) {
             for (int k = 0; k < kRowRegisters; ++k)
-                if (regs != NO_REGISTERS && !shared[v] && held[k] < 0) {
+                if (registers && !shared[v] && held[k] < 0) {
                     held[k] = v;
                     return ROW_ACC + 1 + k;
                 }
@@ -535,7 +533,7 @@ struct RowGen {
         };
         for (int k = 0; k < nops; ++k)
             if (used >> k & 1) {
-                slot[k] = regs == HOLD_ALL ? hold(k) : -1;
+                slot[k] = hold(k);
                 if (slot[k] < 0)
                     slot[k] = take(k);
                 out->slot[k] = (uint8_t)slot[k];
@@ -596,7 +594,7 @@ struct RowGen {
         if ((int)owner.size() > kRowMaxSlots)
             return false;
         out->n = n;
-        out->held = regs != NO_REGISTERS;
+        out->held = registers;
         out->nslots = owner.empty() ? 1 : (int)owner.size();
         return true;
     }
@@ -730,10 +728,9 @@ bool compile_program(const char *text, int nops, const int *kinds,
                     used |= 1u << src;
         if (v.src < nops)
             used |= 1u << v.src;
-        RowGen held = rg, aos = rg;
-        if (used != out->used || !rg.lower(v, used, RowGen::NO_REGISTERS, &out->rows) ||
-            !held.lower(v, used, RowGen::HOLD_ALL, &out->rows_held) ||
-            !aos.lower(v, used, RowGen::HOLD_RESULTS, &out->rows_aos))
+        RowGen held = rg;
+        if (used != out->used || !rg.lower(v, used, false, &out->rows) ||
+            !held.lower(v, used, true, &out->rows_held))
             out->rows.n = 0;
     }
     return true;

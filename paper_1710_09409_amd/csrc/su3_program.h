@@ -157,9 +157,8 @@ struct ProgCode {
     bool scalar_only; // no matrix-valued operand or intermediate
     bool real_only;   // every operand, intermediate and the result real
     unsigned used;    // bit k: operand k is read
-    // row form: every value in a slot, with registers, with registers for
-    // results only
-    RowCode rows, rows_held, rows_aos;
+    // row form: every value in a slot, with registers
+    RowCode rows, rows_held;
 };
 bool compile_program(const char *text, int nops, const int *kinds,
                      ProgCode *out, char *err, size_t errlen);

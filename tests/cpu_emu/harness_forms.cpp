@@ -118,7 +118,7 @@ static void programs()
                     std::vector<double> want(18 * V), got(n * V), over(n * V);
                     oracle_eval_expr(ex.text, ex.n, ex.kinds, qp.data(), want.data(), V);
                     CHECK(su3_program_eval(p, z, f.data(), ex.n, nullptr) == SU3_OK, "%s: %s", ex.text, su3_last_error());
-                    if (l.layout != SU3_LAYOUT_AOS || rk == SU3_KIND_MATRIX) {
+                    if (l.layout != SU3_LAYOUT_AOS) {
                         const bool rows = blockDim.x == 192;  // three waves
                         // (single with four slots: one lane per site)
                         CHECK(rows || arith != SU3_F64, "%s, %lld sites: not by rows", ex.text, (long long)V);
@@ -149,7 +149,7 @@ static void programs()
 static void program_launches()
 {
     struct Case { const char *text; int kinds[4]; int n; int prec; Lay l; int d[4]; bool rows, bypass; };
-    static const Lay soa = {SU3_LAYOUT_SOA, 0};
+    static const Lay soa = {SU3_LAYOUT_SOA, 0}, aos = {SU3_LAYOUT_AOS, 0};
     static const char *const update = "c*a*b+0.5";
     static const Case cases[] = {
         {update, {M, M, R}, 3, SU3_F32, soa, {8, 4, 4, 15}, true, true},   // 1 round, 1
@@ -165,6 +165,14 @@ static void program_launches()
         {"a*b+c*d", {M, M, M, M}, 4, SU3_F32, soa, {24, 24, 24, 18}, false, true},  // 90 MB
         {"a*b+c*d", {M, M, M, M}, 4, SU3_F32, {SU3_LAYOUT_AOSOA, 8}, {8, 8, 8, 8}, false, false},
         {"a*adj(b)", {M, M}, 2, SU3_F32, {SU3_LAYOUT_VNODE, 2}, {4, 4, 4, 4}, true, false},
+        // AoS: products of up to 50 MB per field, three slots in double of up to 35 MB
+        {"a*adj(b)", {M, M}, 2, SU3_F64, aos, {24, 24, 24, 25}, true, false},
+        {"a*adj(b)", {M, M}, 2, SU3_F64, aos, {24, 24, 24, 26}, false, false},
+        {update, {M, M, R}, 3, SU3_F64, aos, {24, 24, 24, 17}, true, false},  // 34 MB
+        {update, {M, M, R}, 3, SU3_F64, aos, {24, 24, 24, 18}, false, false},
+        {"a*b+c*d", {M, M, M, M}, 4, SU3_F64, aos, {4, 4, 4, 4}, false, false},
+        {"(a*b+c*d)*(a*c+b*d)+(a-b)*(c-d)", {M, M, M, M}, 4, SU3_F64, aos, {4, 4, 4, 6}, true, false},  // 6 of 6 at once
+        {"(a*b+c*d)*(a*c+b*d)+(a-b)*(c-d)", {M, M, M, M}, 4, SU3_F64, aos, {4, 4, 4, 7}, false, false},
         {"a+b+a*b", {R, R}, 2, SU3_F32, soa, {8, 8, 8, 8}, false, true},
         {"a+b+a*b", {R, R}, 2, SU3_F64, soa, {8, 8, 8, 8}, false, false}};
     for (const Case &c : cases) {
