@@ -2685,7 +2685,10 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
         }
     }
     size_t turn = 0;
-    su3_launch win = default_launch(expr, prec, layout, std::get<3>(k), s.V);
+    // the call's own launch is the first candidate
+    su3_launch win = dslash ? default_dslash(prec, layout, s.L, dims, simd,
+                                             device_cus(sets[0][0] ? sets[0][0]->device : 0))
+                            : default_launch(expr, prec, layout, std::get<3>(k), s.V);
     double win_us = 1e300;
     // expression programs are timed on the streaming product a*b, those
     // with a scalar result on the trace of a product; where programs of four
@@ -2704,8 +2707,6 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
                            su3_launch *win, double *win_us) {
         const su3_field *f0 = sets[0][0];
         for (su3_launch c : list) {
-            if (expr == SU3_EXPR_CSHIFT && c.schedule)
-                continue;  // a copy has no row phases
             if (program || expr == SU3_EXPR_CSHIFT || expr == SU3_EXPR_MUL_SHIFTED)
                 c.xcd_remap = default_launch(expr, prec, layout, f0->lanes, f0->V).xcd_remap;
             double us = 0;
@@ -2750,11 +2751,18 @@ static su3_status autotune_impl(su3_expr expr, su3_precision prec,
     };
     if (st == SU3_OK) {
         const su3_field *f0 = sets[0][0];
-        sweep(dslash ? dslash_candidates(2 * f0->rbytes, f0->dims[0] / f0->simd[0],
-                                         layout == SU3_LAYOUT_VNODE ? (int)f0->L : 1)
-              : program ? program_list(&prog)
-                        : candidates(layout, expr, prec),
-              &prog, &win, &win_us);
+        std::vector<su3_launch> list =
+            dslash ? dslash_candidates(2 * f0->rbytes, f0->dims[0] / f0->simd[0],
+                                       layout == SU3_LAYOUT_VNODE ? (int)f0->L : 1)
+            : program ? program_list(&prog)
+                      : candidates(layout, expr, prec);
+        if (expr == SU3_EXPR_CSHIFT)  // a copy has no row phases
+            list.erase(std::remove_if(list.begin(), list.end(),
+                                      [](const su3_launch &c) { return c.schedule != 0; }),
+                       list.end());
+        if (!program)
+            list.insert(list.begin(), win);
+        sweep(list, &prog, &win, &win_us);
         if (win_us >= 1e300)
             st = fail(SU3_ERR_HIP, "no candidate launch ran");
     }
@@ -2867,6 +2875,25 @@ struct BatchPlan {
     su3_launch cfg;
 };
 
+static su3_launch default_batch(const su3_expr *exprs, su3_field *const *z, int32_t n)
+{
+    int64_t sites = 0, bytes[4] = {0, 0, 0, 0}, all = 0;
+    for (int i = 0; i < n; ++i) {
+        const int64_t b = site_call_bytes(exprs[i], z[i]->prec, z[i]->V);
+        sites += z[i]->V;
+        bytes[z[i]->prec] += b;
+        all += b;
+    }
+    int prec = SU3_F64;
+    if (4 * bytes[SU3_F64] < 3 * all) {
+        prec = SU3_F32;
+        for (int q : {SU3_F16_F32ACC, SU3_C12_F32})
+            if (bytes[q] > bytes[prec])
+                prec = q;
+    }
+    return default_launch(SU3_EXPR_BATCH + exprs[0], prec, z[0]->layout, z[0]->lanes, sites);
+}
+
 static su3_status plan_batch(const su3_expr *exprs, su3_field *const *z,
                              const su3_field *const *ops, int32_t n,
                              const su3_launch *forced, BatchPlan *plan)
@@ -2878,7 +2905,7 @@ static su3_status plan_batch(const su3_expr *exprs, su3_field *const *z,
     std::vector<BatchItem> &items = plan->items;
     items.assign(n, BatchItem());
     int mode = 0;
-    int64_t total_sites = 0, bytes[4] = {0, 0, 0, 0};
+    int64_t total_sites = 0;
     int dev = -1;
     for (int i = 0; i < n; ++i) {
         const int nops = (exprs[i] >= SU3_EXPR_MUL && exprs[i] <= SU3_EXPR_APB_AB)
@@ -2914,24 +2941,13 @@ static su3_status plan_batch(const su3_expr *exprs, su3_field *const *z,
               (z[i]->prec == SU3_F64 || z[i]->prec == SU3_C12_F32)))
             mode = 1;
         total_sites += z[i]->V;
-        bytes[z[i]->prec] += site_call_bytes(exprs[i], z[i]->prec, z[i]->V);
     }
     su3_launch cfg;
     if (forced) {
         cfg = *forced;
     } else if (!tuned_launch(SU3_EXPR_BATCH + exprs[0], z[0]->prec, z[0]->layout, z[0]->lanes,
                              total_sites, &cfg)) {
-        const int64_t all = bytes[SU3_F64] + bytes[SU3_F32] + bytes[SU3_F16_F32ACC] +
-                            bytes[SU3_C12_F32];
-        int prec = SU3_F64;
-        if (4 * bytes[SU3_F64] < 3 * all) {
-            prec = SU3_F32;
-            for (int q : {SU3_F16_F32ACC, SU3_C12_F32})
-                if (bytes[q] > bytes[prec])
-                    prec = q;
-        }
-        cfg = default_launch(SU3_EXPR_BATCH + exprs[0], prec, z[0]->layout, z[0]->lanes,
-                             total_sites);
+        cfg = default_batch(exprs, z, n);
     }
     const int T = cfg.tile_sites;
     // tile table: item i owns ceil(V_i / T) tiles starting at the exclusive
@@ -3182,17 +3198,23 @@ extern "C" su3_status su3_batch_autotune(const su3_expr *exprs,
     if (!exprs || !z || !ops || n <= 0 || !z[0])
         return fail(SU3_ERR_INVALID_ARG, "NULL argument or empty batch");
     hipStream_t hs = static_cast<hipStream_t>(stream);
+    std::vector<su3_launch> list = batch_candidates();
+    BatchPlan plan;
+    su3_status valid = plan_batch(exprs, z, ops, n, &list[0], &plan);
+    if (valid != SU3_OK)
+        return valid;  // nothing tuned
     int64_t total = 0;
     for (int i = 0; i < n; ++i)
-        if (z[i])
-            total += z[i]->V;
-    su3_launch win = default_launch(exprs[0], z[0]->prec, z[0]->layout, z[0]->lanes, total);
+        total += z[i]->V;
+    // the batch's own launch is the first candidate
+    su3_launch win = default_batch(exprs, z, n);
+    list.insert(list.begin(), win);
     double win_us = 1e300;
-    for (const su3_launch &c : batch_candidates()) {
+    for (const su3_launch &c : list) {
         su3_batch *b = nullptr;
         su3_status st = batch_create(&b, exprs, z, ops, n, stream, &c);
         if (st != SU3_OK)
-            return st;  // invalid items: report, nothing tuned
+            return st;
         double us = 0;
         st = time_launch([&]() { return su3_batch_launch(b, stream); }, hs, 2,
                          5, &us);

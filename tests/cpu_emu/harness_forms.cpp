@@ -305,6 +305,46 @@ static void program_settings()
     std::printf("program settings done\n");
 }
 
+// Where every candidate takes alike, a tuner keeps the call's own launch.
+static void tuners()
+{
+    struct Case { su3_expr e; su3_precision prec; Lay l; };
+    const Lay soa = {SU3_LAYOUT_SOA, 0}, aos = {SU3_LAYOUT_AOS, 0}, short_runs = {SU3_LAYOUT_AOSOA, 8}, vn = {SU3_LAYOUT_VNODE, 4};
+    const Case cases[] = {
+        {SU3_EXPR_MUL, SU3_F64, soa}, {SU3_EXPR_MULADD, SU3_F32, soa}, {SU3_EXPR_MUL, SU3_F64, aos}, {SU3_EXPR_MUL, SU3_F16_F32ACC, short_runs},
+        {SU3_EXPR_MUL, SU3_F32, vn}, {SU3_EXPR_CSHIFT, SU3_F64, soa}, {SU3_EXPR_MUL_SHIFTED, SU3_F64, aos}, {SU3_EXPR_MUL_SHIFTED, SU3_F32, vn},
+        {SU3_EXPR_DSLASH, SU3_F64, soa}, {SU3_EXPR_DSLASH, SU3_F32, vn}, {SU3_EXPR_PROGRAM, SU3_F64, aos}, {SU3_EXPR_PROGRAM_SCALAR, SU3_F64, aos}};
+    const int d[4] = {2, 2, 2, 4};
+    for (const Case &c : cases) {
+        su3_launch was, best, now;
+        su3_launch_reset();
+        CHECK(su3_launch_get(c.e, c.prec, (su3_layout)c.l.layout, c.l.lanes, d, &was) == SU3_OK, "get: %s", su3_last_error());
+        CHECK(su3_autotune(c.e, c.prec, (su3_layout)c.l.layout, c.l.lanes, d, nullptr, &best) == SU3_OK, "autotune: %s", su3_last_error());
+        CHECK(su3_launch_get(c.e, c.prec, (su3_layout)c.l.layout, c.l.lanes, d, &now) == SU3_OK, "get: %s", su3_last_error());
+        CHECK(std::memcmp(&best, &now, sizeof now) == 0, "expr %d: the table holds another launch", c.e);
+        if (c.e == SU3_EXPR_PROGRAM || c.e == SU3_EXPR_PROGRAM_SCALAR) {
+            CHECK(best.schedule == 1, "expr %d: no form", c.e);
+            best.schedule = was.schedule;
+            was.nontemporal = best.nontemporal;  // by the operands' bytes
+        }
+        CHECK(std::memcmp(&best, &was, sizeof was) == 0, "expr %d prec %d layout %d/%d: block %d nontemporal %d cap %d schedule %d, untuned %d %d %d %d", c.e, c.prec, c.l.layout, c.l.lanes,
+              best.block, best.nontemporal, best.occupancy, best.schedule, was.block, was.nontemporal, was.occupancy, was.schedule);
+    }
+    for (const Lay &l : {soa, short_runs}) {
+        su3_field *z = make(d, SU3_F32, M, l, nullptr), *x = make(d, SU3_F32, M, l, nullptr), *y = make(d, SU3_F32, M, l, nullptr);
+        const su3_expr e = SU3_EXPR_MUL;
+        const su3_field *ops[4] = {x, y, nullptr, nullptr};
+        su3_launch was, best;
+        su3_launch_reset();
+        CHECK(su3_launch_get((su3_expr)(SU3_EXPR_BATCH + SU3_EXPR_MUL), SU3_F32, (su3_layout)l.layout, l.lanes, d, &was) == SU3_OK, "get: %s", su3_last_error());
+        CHECK(su3_batch_autotune(&e, &z, ops, 1, nullptr, &best) == SU3_OK, "batch autotune: %s", su3_last_error());
+        CHECK(std::memcmp(&best, &was, sizeof was) == 0, "batch layout %d: tile %d nontemporal %d, untuned %d %d", l.layout, best.tile_sites, best.nontemporal, was.tile_sites, was.nontemporal);
+        for (su3_field *f : {z, x, y}) su3_field_free(f);
+    }
+    su3_launch_reset();
+    std::printf("tuners done\n");
+}
+
 static void traces()
 {
     static const char *const texts[] = {"trace(-a)", "trace(conj(a))", "trace(adj(-a))", "trace(transpose(-conj(a)))", "-trace(a)"};
@@ -528,6 +568,7 @@ int main()
     program_settings();
     programs();
     program_launches();
+    tuners();
     traces();
     hopping();
     t_links();
