@@ -571,16 +571,18 @@ struct Stage {
 static const size_t kStageBytes = (size_t)16 << 20;
 static const size_t kStagesKept = 4;
 static std::mutex g_stage_mu;
-static std::vector<Stage> g_stages;
+static Stage g_stages[kStagesKept];
+static size_t g_nstages = 0;
 
 static bool acquire_stage(int device, size_t bytes, Stage *out)
 {
     {
         std::lock_guard<std::mutex> lk(g_stage_mu);
-        for (size_t i = 0; i < g_stages.size(); ++i)
+        for (size_t i = 0; i < g_nstages; ++i)
             if (g_stages[i].device == device && g_stages[i].bytes >= bytes) {
                 *out = g_stages[i];
-                g_stages.erase(g_stages.begin() + (ptrdiff_t)i);
+                --g_nstages;
+                std::move(g_stages + i + 1, g_stages + g_nstages + 1, g_stages + i);
                 return true;
             }
     }
@@ -597,8 +599,8 @@ static void give_back_stage(Stage s)
 {
     {
         std::lock_guard<std::mutex> lk(g_stage_mu);
-        if (g_stages.size() < kStagesKept) {
-            g_stages.push_back(s);
+        if (g_nstages < kStagesKept) {
+            g_stages[g_nstages++] = s;
             return;
         }
         for (Stage &k : g_stages)  // keep the larger ones
@@ -610,13 +612,16 @@ static void give_back_stage(Stage s)
 
 static void release_stages()
 {
-    std::vector<Stage> free_now;
+    Stage free_now[kStagesKept];
+    size_t n;
     {
         std::lock_guard<std::mutex> lk(g_stage_mu);
-        free_now.swap(g_stages);
+        n = g_nstages;
+        std::copy(g_stages, g_stages + n, free_now);
+        g_nstages = 0;
     }
-    for (const Stage &s : free_now)
-        (void)hipFree(s.ptr);
+    for (size_t i = 0; i < n; ++i)
+        (void)hipFree(free_now[i].ptr);
 }
 
 // Fields of at least this many stored reals are converted on the device;
@@ -1437,17 +1442,24 @@ static su3_launch plan_dslash(int prec, int layout, int64_t L, const int32_t dim
 static su3_launch default_dslash(int prec, int layout, int64_t L, const int32_t dims[4],
                                  const int32_t simd[4], int cus)
 {
+    struct Plan {
+        int32_t key[11];  // zero: none (no extent is)
+        su3_launch c;
+    };
     static std::mutex mu;
-    static std::map<std::array<int32_t, 11>, su3_launch> plans;
-    const std::array<int32_t, 11> key = {prec,    layout,  cus,     dims[0], dims[1], dims[2],
-                                         dims[3], simd[0], simd[1], simd[2], simd[3]};
+    static Plan plans[256];  // by a hash of the key, the newest kept
+    const int32_t key[11] = {prec,    layout,  cus,     dims[0], dims[1], dims[2],
+                             dims[3], simd[0], simd[1], simd[2], simd[3]};
+    uint32_t h = 0;
+    for (int32_t v : key)
+        h = (h ^ (uint32_t)v) * 2654435761u;
     std::lock_guard<std::mutex> lk(mu);
-    auto it = plans.find(key);
-    if (it != plans.end())
-        return it->second;
-    if (plans.size() >= 256)
-        plans.clear();
-    return plans[key] = plan_dslash(prec, layout, L, dims, simd, cus);
+    Plan &p = plans[h >> 24];
+    if (std::memcmp(p.key, key, sizeof key) != 0) {
+        p.c = plan_dslash(prec, layout, L, dims, simd, cus);
+        std::memcpy(p.key, key, sizeof key);
+    }
+    return p.c;
 }
 
 // JSON cache: one object per line with integer fields.

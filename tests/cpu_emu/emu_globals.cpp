@@ -13,6 +13,7 @@ std::vector<std::function<void()>> emu_graph;
 unsigned char emu_lds[1 << 18];
 int emu_launches = 0;
 bool emu_threaded = false;
+bool emu_failing_new = false;
 int emu_atomics = 0, emu_failing_mallocs = 0, emu_frees = 0;
 std::vector<emu_call> emu_calls;
 const char *emu_watch_lo = nullptr, *emu_watch_hi = nullptr;

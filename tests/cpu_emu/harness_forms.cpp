@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
+#include <new>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -19,6 +20,16 @@ int oracle_roundtrip(int prec, const double *in, double *out, int64_t V);
 int oracle_dslash(const double *const *u, const double *in, double *out, const int32_t dims[4]);
 int oracle_eval_expr(const char *text, int nops, const int *kinds, const double *const *fields, double *out, int64_t V);
 }
+
+void *operator new(size_t n)
+{
+    void *p = emu_failing_new ? nullptr : std::malloc(n ? n : 1);
+    if (!p)
+        throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 static int fails = 0;
 #define CHECK(cond, ...)         \
@@ -563,6 +574,30 @@ static void staging()
     std::printf("staging done\n");
 }
 
+// Calls that hold no host memory of their own end well where there is none.
+static void no_host_memory()
+{
+    const int d[4] = {8, 8, 8, 4}, other[4] = {8, 8, 8, 6};
+    const std::vector<double> h = host_values(volume(d), M, 0);
+    std::vector<double> got(h.size());
+    su3_field *f = make(d, SU3_F64, M, {SU3_LAYOUT_SOA, 0}, nullptr);
+    emu_calls.reserve(emu_calls.size() + 100);
+    try {
+        su3_launch c;
+        emu_failing_new = true;
+        const su3_status planned = su3_launch_get(SU3_EXPR_DSLASH, SU3_F64, SU3_LAYOUT_SOA, 0, other, &c);
+        const su3_status up = su3_field_upload(f, h.data(), nullptr), down = su3_field_download(f, got.data(), nullptr);
+        emu_failing_new = false;
+        CHECK(planned == SU3_OK && up == SU3_OK && down == SU3_OK, "plan %d, upload %d, download %d", planned, up, down);
+        CHECK(std::memcmp(got.data(), h.data(), sizeof(double) * h.size()) == 0, "another field than was stored");
+    } catch (const std::bad_alloc &) {
+        emu_failing_new = false;
+        CHECK(false, "an exception crosses the entry point");
+    }
+    su3_field_free(f);
+    std::printf("no host memory done\n");
+}
+
 int main()
 {
     program_settings();
@@ -574,6 +609,7 @@ int main()
     t_links();
     batches();
     staging();
+    no_host_memory();
     std::printf("fails %d\n", fails);
     return fails != 0;
 }

@@ -116,9 +116,12 @@ inline void emu_run(K k, dim3 g, dim3 b, size_t shm, A... a)
     }
 }
 
+extern bool emu_failing_new;  // host allocations fail (not the emulation's own)
+
 template <class K, class... A>
 inline void emu_launch(K k, dim3 g, dim3 b, size_t shm, A... a)
 {
+    const struct Own { bool was = emu_failing_new; Own() { emu_failing_new = false; } ~Own() { emu_failing_new = was; } } own;
     if (shm > (160u << 10)) {  // a compute unit's LDS
         std::fprintf(stderr, "launch with %zu bytes of dynamic LDS\n", shm);
         std::abort();
