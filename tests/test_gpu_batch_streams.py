@@ -60,3 +60,39 @@ def test_streams_and_replays(persistent):
             z.owner.zero_()
         torch.cuda.synchronize()
     su3.su3_batch_destroy(batch)
+
+
+@pytest.mark.parametrize("prec", [F64, su3.SU3_F32, su3.SU3_F16_F32ACC, su3.SU3_C12_F32],
+                         ids=["f64", "f32", "f16", "c12"])
+def test_every_entry(prec):
+    """A batch launched, replayed from a graph and run without a handle writes
+    every entry of every item, and nothing beyond them."""
+    s = torch.cuda.current_stream()
+    lattices = [(2, 3, 5, 7), (8, 8, 8, 8), (12, 12, 12, 13)]
+    zs, ops, want = [], [], []
+    for i, d in enumerate(lattices):
+        hosts = [testgen.su3_field(testgen.volume(d), field_id=80 + 2 * i + k) for k in (0, 1)]
+        x, y = (upload(d, prec, SOA, 0, h, s) for h in hosts)
+        z = su3.field_tensor(d, prec, SOA)
+        z.owner.fill_(0x55)
+        su3.su3_mult(z, x, y, s)
+        want.append(z.owner.clone())
+        zs.append(z)
+        ops.append([x, y])
+    exprs = [su3.SU3_EXPR_MUL] * len(zs)
+    batch = su3.su3_batch_create(exprs, zs, ops, s)
+    graphs = [torch.cuda.CUDAGraph() for _ in range(2)]
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graphs[0]):
+        su3.su3_batch_launch(batch, torch.cuda.current_stream())
+    with torch.cuda.graph(graphs[1]):
+        su3.su3_batch_run(exprs, zs, ops, torch.cuda.current_stream())
+    for go in (lambda: su3.su3_batch_launch(batch, s), graphs[0].replay, graphs[0].replay,
+               graphs[1].replay, lambda: su3.su3_batch_run(exprs, zs, ops, s), graphs[1].replay):
+        for z in zs:
+            z.owner.fill_(0x55)
+        torch.cuda.synchronize()
+        go()
+        torch.cuda.synchronize()
+        assert all(torch.equal(z.owner, w) for z, w in zip(zs, want))
+    su3.su3_batch_destroy(batch)
