@@ -1615,7 +1615,8 @@ static su3_status validate_item(const su3_field *z, int expr,
 
 // ------------------------------------------------------------ compute
 
-// LDS one staged workgroup may take (operand tiles, reused for the result).
+// What a staged launch may count, a tile per operand.  The kernel passes all of
+// them through one tile; settings beyond the limit stay refused all the same.
 static const size_t kLdsStageMaxBytes = 65536;
 
 static su3_status launch_item(su3_field *z, int expr,
@@ -1635,8 +1636,8 @@ static su3_status launch_item(su3_field *z, int expr,
         const size_t shm = (size_t)n_ops * c.block * z->E * 2 * z->rbytes;
         if (shm > kLdsStageMaxBytes)
             return fail(SU3_ERR_UNSUPPORTED,
-                        "LDS staging of %d operands x %d sites needs %zu bytes "
-                        "of LDS (limit %zu)", n_ops, c.block, shm,
+                        "LDS staging of %d operands x %d sites counts %zu bytes "
+                        "(limit %zu)", n_ops, c.block, shm,
                         kLdsStageMaxBytes);
         const int64_t tiles = (z->V + c.block - 1) / c.block;
         int64_t grid = tiles;
@@ -2445,17 +2446,18 @@ static std::vector<su3_launch> candidates(int layout, int expr, int prec)
     c.sites_per_lane = 0;
     if (layout == SU3_LAYOUT_AOS) {
         for (int b : {64, 128, 256})
-            for (int nt : {0, 3, 7})
-                for (int lds = 0; lds < 2; ++lds) {
-                    if (lds && (b > 128 || nt == 7))
-                        continue;
-                    c.block = b;
-                    c.nontemporal = nt;
-                    c.lds_stage = lds;
-                    c.occupancy = 0;
-                    c.schedule = 0;
-                    out.push_back(c);
-                }
+            for (int nt : {0, 2, 3, 7})
+                for (int lds = 0; lds < 2; ++lds)
+                    for (int occ : {0, 3, 5, 8}) {
+                        if (lds ? b > 128 : occ || nt == 2)
+                            continue;
+                        c.block = b;
+                        c.nontemporal = nt;
+                        c.lds_stage = lds;
+                        c.occupancy = occ;
+                        c.schedule = 0;
+                        out.push_back(c);
+                    }
         return out;
     }
     const bool site = expr >= SU3_EXPR_MUL && expr <= SU3_EXPR_APB_AB;
@@ -3164,7 +3166,7 @@ extern "C" su3_status su3_batch_destroy(su3_batch *b)
 
 // Candidate launches of the batch autotuner: for each tile size, one-shot
 // grids (one workgroup per tile: blocks of 64 or 128, occupancy caps,
-// schedules, nontemporal or streaming stores) and persistent grids drawing
+// schedules, cached, nontemporal or streaming) and persistent grids drawing
 // the tiles from the ticket counter (blocks of 64 or 256, 2-8 workgroups
 // per CU, streaming stores).
 static std::vector<su3_launch> batch_candidates()
@@ -3180,7 +3182,7 @@ static std::vector<su3_launch> batch_candidates()
         for (int b : {64, 128})
             for (int occ : {0, 4, 6})
                 for (int sched : {0, 1})
-                    for (int nt : {3, 7}) {
+                    for (int nt : {0, 3, 7}) {
                         c.block = b;
                         c.occupancy = occ;
                         c.schedule = sched;
