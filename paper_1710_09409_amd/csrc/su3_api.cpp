@@ -1040,7 +1040,9 @@ static su3_launch default_launch(int expr, int prec, int layout, int lanes, int6
         // (FP32 24^3 x 48: 24.7 us against 35.1 with 5; half 48^4 98.6
         // against 220).  Double needs fewer the larger the call (product
         // 48^4: 5 waves 377 us, 10 waves 391; 24^3 x 48: 10 waves 49.8 us, 5
-        // waves 52.7; copy 48^4 6 waves 254, 5 waves 262).  Stores and loads
+        // waves 52.7; copy 48^4 6 waves 254, 5 waves 262), and stores past L2 too
+        // from there on only (30^4 59.2 us, with streaming stores 62.2; 36^4 121
+        // and 116).  Stores and loads
         // are cached below 64 to 100 MB (half copy 32^4: 12 us against 19).
         // AoS reads every line once per entry, so its loads always stay
         // cached (FP64 32^4: 103 us against 452).
@@ -1058,7 +1060,7 @@ static su3_launch default_launch(int expr, int prec, int layout, int lanes, int6
         } else if (dbl && product && bytes > 100 * MB) {
             c.block = bytes > 200 * MB && bytes <= 512 * MB ? 128 : 64;
             c.occupancy = bytes > 200 * MB ? 5 : 0;
-            c.nontemporal = bytes > 200 * MB ? 7 : 3;
+            c.nontemporal = bytes > 512 * MB ? 7 : 3;
         } else if (dbl && !product) {
             c.block = 128;
             c.occupancy = bytes <= 64 * MB ? 5 : 3;

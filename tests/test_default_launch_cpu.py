@@ -39,3 +39,10 @@ def test_pieces_of_64_bytes(prec, layout, lanes):
 def test_whole_lines(layout, lanes):
     for expr in (MUL, SHIFT, COPY, su3.SU3_EXPR_BATCH + MUL):
         assert _nt(expr, F64, layout, lanes) & 1 == 1
+
+
+def test_double_product_streams_its_stores_late():
+    """From 512 MB on: below, nontemporal stores are as fast or faster."""
+    assert _nt(SHIFT, F64, SOA, 0, (28, 28, 28, 28)) == 3
+    assert _nt(SHIFT, F64, SOA, 0, (32, 32, 32, 32)) == 3
+    assert _nt(SHIFT, F64, SOA, 0, (36, 36, 36, 36)) == 7
