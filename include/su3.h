@@ -160,7 +160,8 @@ typedef struct su3_program su3_program;
  *               link loads only; the LDS-tiled walks take no heed of it:
  *               they store nontemporal and load cached, but for the
  *               t-links, each read once per walk, in layouts whose
- *               lane-blocks hold whole 128-byte lines)
+ *               lane-blocks hold whole 128-byte lines and calls above
+ *               330 MB)
  *   xcd_remap   1: hand each of the 8 XCDs a contiguous range of
  *               workgroups instead of the hardware's round-robin;
  *               2 (su3_dslash's LDS-tiled walks): each XCD walks one

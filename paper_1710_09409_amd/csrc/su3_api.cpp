@@ -2066,7 +2066,7 @@ static const RowCode *row_code(const su3_program *p, const su3_field *z, int ari
 {
     const ProgCode &pc = p->code;
     const bool aos = z->layout == SU3_LAYOUT_AOS;
-    if (pc.rows.n == 0)
+    if (pc.rows.n == 0)  // more slots than there are: no known expression
         return nullptr;
     // AoS matrices without a matrix to store: the one-lane kernel's cached
     // loads reach the rest of a site's record in the same lines (FP64 32^4
